@@ -166,13 +166,12 @@ static_assert(sizeof(KernelArgs) <= 4096, "kernel arguments");
 // Fused base projection (Eq. 1 whole): y = x W + s_g (x A_g) B_g for every
 // row, one MFMA GEMM over square tiles of kBaseBig or kBaseSmall rows x as
 // many columns, the adapter delta added in the tile's epilogue from a float32
-// v computed beforehand.  A stage holds the tile's x and W slices over
-// kBaseStageBytes / (4 tile) of K: 64 along K for the big tile (one
-// 128-byte line per row), 128 for the small one.
+// v computed beforehand.  K ranges are counted in stages of kBaseStageBytes of
+// the tile's x and W: 64 along K for the big tile (one 128-byte line per row),
+// 128 for the small one (two steps of the kernel's pipeline).
 // ---------------------------------------------------------------------------
 constexpr int kBaseBig = 256;            // tile edge while whole tiles fill the compute units
 constexpr int kBaseSmall = 128;          // tile edge of launches with fewer big tiles than compute units
-constexpr int kBaseThreads = 256;        // 4 wave64: 2 (rows) x 2 (columns), each a quarter of the tile
 constexpr int kBaseStageBytes = 64 * 1024;   // x slice, then W slice
 constexpr int kBaseMinSplitStages = 8;   // fewest K stages of a split range
 constexpr int kBaseLoraRanks = 64;       // ranks of B_g staged in LDS at a time (one stage buffer)
