@@ -249,9 +249,9 @@ def measure(torch, w, dev, steps, warmup, rotate_mib, label):
 
 
 def plan_update_cost(torch, w, dev, n=400):
-    """Host time of re-planning a step (lora_plan_update: grouping, work
-    list, staging copy, enqueue of the upload and the arming fill) and the
-    device time of that upload, alternating between the workload's batch and
+    """Host time of re-planning a step (lora_plan_update: grouping, row
+    blocks, enqueue of the kernel that writes the list and arms the step) and the
+    device time of that kernel, alternating between the workload's batch and
     a second batch of the same size drawn with another seed."""
     from paper_2401_11240_amd import device as D
     from paper_2401_11240_amd import lora as L
@@ -293,7 +293,7 @@ def measure_base(torch, name, dev, steps, rotate_mib):
     (the shrink into float32 v, its reduction, the MFMA GEMM with the delta in
     its epilogue, the reduction of split tiles), captured in a HIP graph and
     replayed between HIP events; the eager per-call form (lora_base_apply,
-    which plans and uploads its work list every call) is timed beside it."""
+    which plans and writes its work list every call) is timed beside it."""
     from paper_2401_11240_amd import device as D
     from paper_2401_11240_amd import lora as L
     from paper_2401_11240_amd import workloads as W

@@ -134,15 +134,14 @@ int lora_expand(lora_table_t t, const lora_batch_t* b, const float* v, int64_t l
 
 /*
  * The whole delta in one call: y[t,:] <- round(y[t,:] + s_g (x[t,:].A_g).B_g).
- * The float32 intermediate lives only in ws.  Uploads the plan of this batch
- * into ws, then runs the kernels; no host synchronisation.
+ * The float32 intermediate lives only in ws.  Writes the work list of this
+ * batch into ws (a kernel whose arguments hold the batch's row blocks), then
+ * runs the kernels; no copy and no host synchronisation.
  *
- * lora_shrink, lora_expand and lora_apply_fused upload their work list from a
- * small ring of pinned host buffers that later calls reuse (the host waits on
- * a slot only when 16 uploads are still in flight).  A graph replay would copy
- * whatever the slot holds by then, so these three calls refuse a stream that
- * is being captured: LORA_E_CAPTURE, nothing enqueued.  Record the lora_plan_*
- * calls instead.
+ * lora_shrink, lora_expand and lora_apply_fused write a work list that other
+ * launches of the caller may be made for, so these three calls refuse a stream
+ * that is being captured: LORA_E_CAPTURE, nothing enqueued.  Record the
+ * lora_plan_* calls instead.
  */
 int lora_apply_fused(lora_table_t t, const lora_batch_t* b, const void* x, int64_t ldx, void* y,
                      int64_t ldy, void* ws, size_t ws_bytes, void* stream);
@@ -168,9 +167,8 @@ int lora_apply_fused(lora_table_t t, const lora_batch_t* b, const void* x, int64
  * depend on timing), then rounds.  Meant for prompt segments (rows of one
  * adapter run together); decode tokens work, each adapter run of a tile
  * costing one epilogue pass.  ws: device workspace of
- * lora_base_workspace_bytes(t, b) bytes, any contents.  Uploads its work list
- * through the same reused pinned ring as lora_apply_fused, so it refuses a
- * capturing stream (LORA_E_CAPTURE).  Errors as lora_apply_fused's, plus wt
+ * lora_base_workspace_bytes(t, b) bytes, any contents.  Writes its work list
+ * as lora_apply_fused does, so it refuses a capturing stream (LORA_E_CAPTURE).  Errors as lora_apply_fused's, plus wt
  * and y must not overlap (LORA_E_OVERLAP).
  */
 int lora_base_workspace_bytes(lora_table_t t, const lora_batch_t* b, size_t* bytes);
@@ -181,7 +179,7 @@ int lora_base_apply(lora_table_t t, const lora_batch_t* b, const void* x, int64_
  * lora_base_apply planned once for a batch (the same batch runs every layer
  * of a prompt step, Section 2.2): lora_base_plan_create builds the work list
  * and the tile pieces, allocates the plan's device memory (work list, float32
- * v, partial tiles) and uploads them, synchronising `stream` once; it refuses
+ * v, partial tiles) and fills it, synchronising `stream` once; it refuses
  * a capturing stream.  lora_base_plan_apply then enqueues kernels only (the
  * shrink, its reduction into v, the GEMM, and the reduction of split tiles)
  * and may be recorded in a HIP graph; it runs on any table whose shapes,
@@ -203,10 +201,9 @@ int lora_base_plan_destroy(lora_base_plan_t p);
  * (one per GPU the library runs on, held until the process ends); a batch
  * whose workspace (lora_workspace_bytes) exceeds it returns LORA_E_WORKSPACE
  * with nothing enqueued.  The first call on a device looks up the array's
- * device address.  The work list is copied from pageable host memory, which
- * HIP performs synchronously: the call returns once the copy is done, after
- * the stream's earlier work.  Every call on one GPU shares that GPU's array:
- * calls that overlap on one GPU (other streams, other threads) race and must
+ * device address.  The call returns without waiting for the GPU.  Every call on
+ * one GPU shares that GPU's array: calls that overlap on one GPU (other
+ * streams, other threads) race and must
  * be ordered by the caller.  A capturing stream is refused (LORA_E_CAPTURE).
  * Results are those of lora_apply_fused, bit for bit; arguments and errors as
  * there.
@@ -218,9 +215,9 @@ int lora_apply_fused_static(lora_table_t t, const lora_batch_t* b, const void* x
  * Plan a batch once and apply it many times: the batch of a step is the same
  * for every adapted projection of every layer, so the grouping and the work
  * list are built once.  lora_plan_create validates the batch, builds the
- * rank-bucketed work list on the host from table t's ranks and shapes and
- * uploads it, with its own workspace, to device memory owned by the plan
- * (allocates; not for the hot loop).
+ * rank-bucketed work list from table t's ranks and shapes, with its own
+ * workspace, in device memory owned by the plan (allocates; not for the hot
+ * loop).
  *
  * lora_plan_apply runs the whole delta (lora_apply_fused without the upload)
  * with the adapters of table t, or of the table the plan was made with when t
@@ -258,24 +255,22 @@ int lora_plan_create(lora_plan_t* out, lora_table_t t, const lora_batch_t* b, vo
 
 /*
  * Re-planning for continuous batching (Section 2.2: the batch changes every
- * iteration).  A plan owns a fixed amount of device memory and two pinned
- * host staging buffers of the same size, allocated at creation:
- * lora_plan_create sizes them for its batch, lora_plan_create_reserved for at
- * least min_bytes (lora_plan_bytes tells what one batch needs; take the
+ * iteration).  A plan owns a fixed amount of device memory, allocated at
+ * creation: lora_plan_create sizes it for its batch, lora_plan_create_reserved
+ * for at least min_bytes (lora_plan_bytes tells what one batch needs; take the
  * largest over the batches to come).  lora_plan_update plans batch b against
  * table t (NULL: the plan's table, which t then replaces) into that memory:
- * it validates b, builds the work list on the host, copies it into the next
- * staging buffer, enqueues one host-to-device copy and a small fill kernel
- * that arms the step buffers, and returns.  No device or host allocation, no
- * memset, no stream synchronisation (the host waits only when it is two
- * updates ahead of the stream's copies).  A batch that needs more than the
+ * it validates b, cuts it into row blocks on the host and enqueues the kernel
+ * that writes the work list and arms the step buffers (its arguments hold the
+ * row blocks: one launch for about 60 of them), and returns.  No device or host
+ * allocation, no copy, no memset, no synchronisation.  A batch that needs more than the
  * capacity returns LORA_E_WORKSPACE and leaves the plan as it was; errors of
  * b are those of lora_plan_create.  Updates and the plan's launches must be
  * ordered on one stream.  lora_plan_update also clears the plan's status.
  *
  * Graphs.  lora_plan_apply, _shrink and _expand may be recorded in a HIP graph:
  * the record holds the launch of the batch planned at that moment.  Every
- * upload stamps the work list with a new generation, and a launch carries the
+ * update stamps the work list with a new generation, and a launch carries the
  * generation it was made for: a replay after lora_plan_update finds another
  * generation in the plan's header, does nothing (y untouched), and leaves
  * LORA_E_STALE for lora_plan_status.  Record again after re-planning.

@@ -19,6 +19,7 @@
 
 #include "lora.h"
 #include "lora_internal.h"
+#include "lora_plan.h"
 
 namespace lora {
 hipError_t launch_shrink(const KernelArgs& a, const uint32_t* hdr, int dtype, hipStream_t s);
@@ -31,6 +32,89 @@ int set_error(int code, const std::string& msg);
 }  // namespace lora
 
 using namespace lora;
+
+namespace lora {
+
+__global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a) {
+    // read through the argument segment: a lane-dependent index into the
+    // parameter would copy it to private memory
+    const unsigned char* args = (const unsigned char*)__builtin_amdgcn_kernarg_segment_ptr();
+    const uint32_t* data = (const uint32_t*)(args + offsetof(PlanArgs, data));
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    const int t = threadIdx.x;
+    if ((int)blockIdx.x >= a.n_rows) {
+        if (a.first) {
+            if (t < kHeaderBytes / 4) ((uint32_t*)a.w)[t] = t == 0 ? a.generation : 0u;
+            const uint16_t* count = (const uint16_t*)(args + offsetof(PlanArgs, step_count));
+            u32x4* step = (u32x4*)(a.w + a.off_step);
+            for (int q = t; q < 8 * a.step_len * a.n_xcd; q += kThreads)
+                if ((q >> 3) / a.n_xcd >= (int)count[(q >> 3) % a.n_xcd]) step[q] = u32x4{0u, 0u, 0u, 0u};
+        }
+        for (int q = t; q < a.blob_words; q += kThreads) ((uint32_t*)(a.w + a.off_blob))[q] = data[a.blob_at + q];
+        return;
+    }
+    const PlanRow r = ((const PlanRow*)data)[blockIdx.x];
+    const int32_t* rows = (const int32_t*)data + a.n_rows * kRowWords + (r.row0 >= 0 ? 0 : -1 - r.row0);
+    const PlanDims d = *(const PlanDims*)(args + offsetof(PlanArgs, dims) + r.proj() * sizeof(PlanDims));
+    const RowGeom g = row_geom(d, r.rank(), r.nrows());
+    const DevItem base = row_item(r, g, a.row_first + blockIdx.x, rows);
+    const int n_reduce = g.direct ? 0 : g.nslice;
+    const int total = g.nsplit + n_reduce + g.ntiles + g.nslice;
+    const int part = t & 7;                   // this thread's 16 bytes of an item
+    for (int q = t >> 3; q < total; q += kThreads / 8) {
+        DevItem it = base;
+        int c = q, at, queue = -1;            // place in its list, and in its XCD's queue
+        uint64_t list;
+        if (c < g.nsplit) {
+            to_shrink(it, d, g, c);
+            list = a.off_shrink;
+            at = r.shrink_at + c;
+            queue = r.step_shrink + c;
+        } else if ((c -= g.nsplit) < n_reduce) {
+            to_reduce(it, g, c);
+            list = a.off_reduce;
+            at = r.reduce_at + c;
+            queue = r.step_reduce + c;
+        } else if ((c -= n_reduce) < g.ntiles) {
+            to_expand(it, d, g, c);
+            list = a.off_expand;
+            at = r.expand_at + c;
+            queue = r.step_expand + c;
+        } else {
+            c -= g.ntiles;
+            to_reduce(it, g, c);
+            list = a.off_all;
+            at = r.all_at + c;
+        }
+        const uint64_t fp = (uint64_t)it.part;
+        u32x4 v = {(uint32_t)fp, (uint32_t)(fp >> 32), (uint32_t)it.kind, (uint32_t)it.group};
+        if (part == 1) v = u32x4{(uint32_t)it.adapter, (uint32_t)it.rank, (uint32_t)it.nrows, (uint32_t)it.lo};
+        if (part == 2) v = u32x4{(uint32_t)it.len, (uint32_t)it.sub, (uint32_t)it.nsplit, (uint32_t)it.p0};
+        if (part == 3) v = u32x4{(uint32_t)it.pstride, (uint32_t)it.rb, (uint32_t)it.nexp, (uint32_t)it.row0};
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            if (part == 4 + h)
+                v = u32x4{(uint32_t)it.rows[4 * h], (uint32_t)it.rows[4 * h + 1], (uint32_t)it.rows[4 * h + 2],
+                          (uint32_t)it.rows[4 * h + 3]};
+        ((u32x4*)(a.w + list))[8 * (int64_t)at + part] = v;
+        if (a.step_len && queue >= 0) ((u32x4*)(a.w + a.off_step))[8 * ((int64_t)queue * a.n_xcd + r.home) + part] = v;
+    }
+    int32_t* perm = (int32_t*)(a.w + a.off_perm) + r.p0;
+    if (r.proj() == 0 && t < r.nrows()) perm[t] = r.row0 >= 0 ? r.row0 + t : rows[t];
+    if (a.arm) {
+        if (t == 0) ((uint32_t*)(a.w + a.off_sync))[(int64_t)(a.row_first + blockIdx.x) * kSyncStride] = 0u;
+        // the row block's partial and v blocks in both step buffers: the sentinel
+        float* p0 = (float*)(a.w + a.off_step_partials) + r.part;
+        const int n4 = (g.nsplit + 1) * g.pstride / 4;
+        const u32x4 s4 = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+        for (int q = t; q < n4; q += kThreads) {
+            ((u32x4*)p0)[q] = s4;
+            ((u32x4*)(p0 + a.pbuf))[q] = s4;
+        }
+    }
+}
+
+}  // namespace lora
 
 namespace {
 
@@ -106,22 +190,22 @@ struct HostPlan {
     int n_groups = 0;
     int r_max = 0;
     int n_rb = 0;                       // row blocks
-    int n_proj = 1;                     // projections sharing x that one launch runs (copies of the lists)
+    int n_proj = 1;                     // projections sharing x that one launch runs (their lists one after the other)
     std::vector<int> proj_h_out;        // their h_out (n_proj > 1)
     std::vector<int64_t> rb_bytes;      // bytes each row block streams
     std::vector<int32_t> perm, group_off, group_adapter, group_rank;
-    std::vector<DevItem> shrink, expand, reduce, reduce_all, step;
+    std::vector<PlanRow> rows;          // the row blocks (row0 -1: their rows are perm[p0 ..])
+    PlanDims dims[kMaxProj];
+    int n_shrink = 0, n_reduce = 0, n_expand = 0, n_all = 0;   // items of each list (n_all: lora_shrink's reduce items)
+    int n_xcd = 1, step_len = 0;        // step grid laid out per XCD: slots per XCD (0: the lists' own order)
+    uint16_t step_count[64];            // items in each XCD's queue
     int n_rows = 0;
     int64_t n_partials = 0;
     size_t off_shrink = 0, off_expand = 0, off_reduce = 0, off_reduce_all = 0, off_step = 0, off_perm = 0;
     size_t plan_bytes = 0, off_partials = 0, off_sync = 0, sync_bytes = 0, total_bytes = 0;
     size_t off_step_partials = 0, step_partials_bytes = 0, plan_total_bytes = 0;
     uint32_t generation = 0;            // header word 0 of the uploaded work list
-    std::vector<unsigned char> blob;    // [header][item lists][perm], as uploaded
-    void set_generation(uint32_t g) {
-        generation = g;
-        std::memcpy(blob.data(), &g, sizeof g);
-    }
+    int n_step() const { return step_len ? step_len * n_xcd : n_shrink + n_reduce + n_expand; }
 };
 
 int validate_batch(const lora_batch_t* b, int n_adapters) {
@@ -188,17 +272,12 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
     p.n_active = p.n_groups ? p.group_off[p.n_groups] : 0;
     p.group_rank.assign(p.n_groups, 0);
     p.r_max = 0;
-    p.shrink.clear();
-    p.expand.clear();
-    p.reduce.clear();
-    p.reduce_all.clear();
     p.n_rows = b->n_rows;
-    p.step.clear();
-    std::vector<int64_t>& rb_bytes = p.rb_bytes;
-    rb_bytes.clear();
+    p.rows.clear();
+    p.rb_bytes.clear();
     p.n_proj = 1;
     p.n_partials = 0;
-    p.n_rb = 0;
+    p.n_shrink = p.n_reduce = p.n_expand = p.n_all = 0;
 
     // Row blocks of more than 16 rows (prompt segments, popular adapters) are
     // cut into about kTargetItems / (number of such blocks) K ranges: few
@@ -212,19 +291,11 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
         for (int q0 = 0; q0 < n; q0 += rb)
             if (std::min(rb, n - q0) > kInlineRows) ++big_blocks;
     }
-    const int big_split = big_blocks ? std::max(1, (kTargetItems + big_blocks - 1) / big_blocks) : 1;
-    // K ranges and column tiles of a row block of nb rows at rank r
-    auto splits = [&](int r, int nb, int& sub, int& krange, int& nsplit, int& nlen, int& ntiles) {
-        sub = shrink_sub(r, nb);
-        krange = sub;
-        if (nb > kInlineRows) {
-            const int per = (t->h_in + big_split - 1) / big_split;
-            krange = round_up_i(std::max(per, sub), sub);
-        }
-        nsplit = (t->h_in + krange - 1) / krange;
-        nlen = expand_nlen(r, nb);
-        ntiles = (t->h_out + nlen - 1) / nlen;
-    };
+    PlanDims& d = p.dims[0];
+    d.h_in = t->h_in;
+    d.h_out = t->h_out;
+    d.big_split = big_blocks ? std::max(1, (kTargetItems + big_blocks - 1) / big_blocks) : 1;
+    d.small_step = 0;
     // A step whose shrink and expand items fit one round of workgroups
     // (decode) lets expand items add small partial blocks themselves, one hop
     // fewer on its critical path; larger steps add them in reduce items,
@@ -236,101 +307,47 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
         const int rb = row_block(r);
         const int n = p.group_off[g + 1] - p.group_off[g];
         for (int q0 = 0; q0 < n; q0 += rb) {
-            int sub, krange, nsplit, nlen, ntiles;
-            splits(r, std::min(rb, n - q0), sub, krange, nsplit, nlen, ntiles);
-            step_items += nsplit + ntiles;
+            const RowGeom q = row_geom(d, r, std::min(rb, n - q0));
+            step_items += q.nsplit + q.ntiles;
         }
     }
-    const bool small_step = step_items <= kTargetItems;
+    d.small_step = step_items <= kTargetItems;
 
     for (int g = 0; g < p.n_groups; ++g) {
-        const DevAdapter& ad = t->host[p.group_adapter[g]];
-        const int r = ad.rank;
-        const int rv = rank_stride(r);
+        const int r = t->host[p.group_adapter[g]].rank;
         p.group_rank[g] = r;
         p.r_max = std::max(p.r_max, r);
         const int rb = row_block(r);
         for (int p0 = p.group_off[g]; p0 < p.group_off[g + 1]; p0 += rb) {
             const int nb = std::min(rb, p.group_off[g + 1] - p0);
-            int sub, krange, nsplit, nlen, ntiles;
-            splits(r, nb, sub, krange, nsplit, nlen, ntiles);
-            const int pstride = nb * rv;              // one partial (or v) block: [nb][rv] floats
-            DevItem base{};
-            base.rb = p.n_rb++;
-            rb_bytes.push_back((int64_t)(r + nb) * t->h_in * 2 + (int64_t)(r + 2 * nb) * t->h_out * 2);
-            base.nexp = ntiles;
-            base.group = g;
-            base.adapter = p.group_adapter[g];
-            base.rank = r;
-            base.nrows = nb;
-            base.nsplit = nsplit;
-            base.p0 = p0;
-            base.pstride = pstride;
-            if (nb <= kInlineRows)
-                for (int i = 0; i < nb; ++i) base.rows[i] = p.perm[p0 + i];
-            base.row0 = p.perm[p0];
-            for (int i = 1; i < nb; ++i)
-                if (p.perm[p0 + i] != p.perm[p0] + i) {
-                    base.row0 = -1;
-                    break;
-                }
+            const RowGeom q = row_geom(d, r, nb);
+            if ((!shrink_uses_dma(r, nb) && shrink_lds_bytes(r, q.sub, nb) > kShrinkLds) || !expand_fits_lds(r, nb))
+                return fail(LORA_E_SHAPE, "internal: a tile exceeds LDS");
+            PlanRow row{};
+            row.group = g;
+            row.adapter = p.group_adapter[g];
+            row.shape = r | nb << 16;
+            row.p0 = p0;
+            // the last row is nb - 1 past the first only when all are consecutive (rows ascend)
+            row.row0 = p.perm[p0 + nb - 1] == p.perm[p0] + nb - 1 ? p.perm[p0] : -1;
+            if ((uint64_t)(p.n_partials + (int64_t)(q.nsplit + 1) * q.pstride) * 4 > kMaxSpan)
+                return fail(LORA_E_SHAPE, "batch too large: its partial results exceed 2 GiB");
+            row.part = (uint32_t)p.n_partials;
+            row.shrink_at = p.n_shrink;
+            row.reduce_at = p.n_reduce;
+            row.expand_at = p.n_expand;
+            row.all_at = p.n_all;
+            p.n_shrink += q.nsplit;
+            p.n_reduce += q.direct ? 0 : q.nslice;
+            p.n_expand += q.ntiles;
+            p.n_all += q.nslice;
             // the row block's nsplit partial blocks, then its v block
-            const int64_t part0 = p.n_partials;
-            p.n_partials += (int64_t)(nsplit + 1) * pstride;
-            // small partial blocks of a small step are added up by the expand items themselves
-            const bool direct =
-                small_step && nsplit <= kDirectSplits && (int64_t)nsplit * pstride * 4 <= kDirectBytes;
-            for (int c = 0; c < nsplit; ++c) {
-                DevItem it = base;
-                it.kind = kItemShrink;
-                it.part = part0 + (int64_t)c * pstride;
-                it.lo = c * krange;
-                it.len = std::min(krange, t->h_in - c * krange);
-                it.sub = shrink_uses_dma(r, nb) ? shrink_stage_sub(r, nb) : sub;
-                if (!shrink_uses_dma(r, nb) && shrink_lds_bytes(r, sub, nb) > kShrinkLds)
-                    return fail(LORA_E_SHAPE, "internal: shrink tile exceeds LDS");
-                p.shrink.push_back(it);
-            }
-            // reduce slices: at most kReduceBytes of partial values each; G
-            // split groups share a float4 position (G * positions <= threads),
-            // each thread adding at most kMaxSplitLoads blocks
-            int gmin = 1;
-            while (gmin * kMaxSplitLoads < nsplit) gmin *= 2;
-            const int64_t pbytes = (int64_t)nsplit * pstride * 4;
-            int nslice = (int)std::max<int64_t>(1, (pbytes + kReduceBytes - 1) / kReduceBytes);
-            int slen = round_up_i((pstride + nslice - 1) / nslice, 4);
-            slen = std::min(slen, 4 * (kThreads / gmin));
-            nslice = (pstride + slen - 1) / slen;
-            for (int c = 0; c < nslice; ++c) {
-                DevItem it = base;
-                it.kind = kItemReduce;
-                it.part = part0;
-                it.lo = c * slen;
-                it.len = std::min(slen, pstride - c * slen);
-                const int np = it.len / 4;
-                int G = 1;
-                // a row block whose expand items add the partial blocks up
-                // themselves adds them in order 0..nsplit-1: one group here too
-                while (!direct && 2 * G <= nsplit && 2 * G * np <= kThreads) G *= 2;
-                if (G * kMaxSplitLoads < nsplit) return fail(LORA_E_SHAPE, "internal: reduce slice too wide");
-                it.sub = G;
-                p.reduce_all.push_back(it);         // lora_shrink's reduce into the caller's v
-                if (!direct) p.reduce.push_back(it);
-            }
-            for (int c = 0; c < ntiles; ++c) {
-                DevItem it = base;
-                it.kind = kItemExpand;
-                it.part = part0;
-                it.sub = direct ? 1 : 0;
-                it.lo = c * nlen;
-                it.len = std::min(nlen, t->h_out - c * nlen);
-                if (!expand_fits_lds(r, nb))
-                    return fail(LORA_E_SHAPE, "internal: expand tile exceeds LDS");
-                p.expand.push_back(it);
-            }
+            p.n_partials += (int64_t)(q.nsplit + 1) * q.pstride;
+            p.rb_bytes.push_back((int64_t)(r + nb) * t->h_in * 2 + (int64_t)(r + 2 * nb) * t->h_out * 2);
+            p.rows.push_back(row);
         }
     }
-
+    p.n_rb = (int)p.rows.size();
     return LORA_OK;
 }
 
@@ -338,32 +355,32 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
 // carries c in its kind, its own partial and v blocks and its own row block
 // counters (offsets past the projections before it).  Each projection's
 // items wait only on items of the same projection.
-void append_lists(HostPlan& p, const HostPlan& q, int c) {
-    const int64_t np = p.n_partials;
-    const int nrb = p.n_rb;
-    auto app = [&](std::vector<DevItem>& dst, const std::vector<DevItem>& src) {
-        for (DevItem it : src) {
-            it.kind |= c << kProjShift;
-            it.part += np;
-            it.rb += nrb;
-            dst.push_back(it);
-        }
-    };
-    app(p.shrink, q.shrink);
-    app(p.reduce, q.reduce);
-    app(p.expand, q.expand);
-    app(p.reduce_all, q.reduce_all);
+int append_lists(HostPlan& p, const HostPlan& q, int c) {
+    if ((uint64_t)(p.n_partials + q.n_partials) * 4 > kMaxSpan)
+        return fail(LORA_E_SHAPE, "batch too large: its partial results exceed 2 GiB");
+    for (PlanRow r : q.rows) {
+        r.shape |= c << 24;
+        r.part += (uint32_t)p.n_partials;
+        r.shrink_at += p.n_shrink;
+        r.reduce_at += p.n_reduce;
+        r.expand_at += p.n_expand;
+        r.all_at += p.n_all;
+        p.rows.push_back(r);
+    }
+    p.dims[c] = q.dims[0];
+    p.n_shrink += q.n_shrink;
+    p.n_reduce += q.n_reduce;
+    p.n_expand += q.n_expand;
+    p.n_all += q.n_all;
     p.rb_bytes.insert(p.rb_bytes.end(), q.rb_bytes.begin(), q.rb_bytes.end());
     p.n_partials += q.n_partials;
     p.n_rb += q.n_rb;
+    return LORA_OK;
 }
 
-// The grid layout and the device layout of the lists, and the upload image.
+// The grid layout and the device layout of the lists.
 int plan_layout(const lora_table_s* t, HostPlan& p) {
     const std::vector<int64_t>& rb_bytes = p.rb_bytes;
-    if ((uint64_t)p.n_partials * 4 > kMaxSpan)
-        return fail(LORA_E_SHAPE, "batch too large: its partial results exceed 2 GiB");
-
     // A step small enough to run in one round of workgroups (decode) gets a
     // grid laid out per XCD: workgroup p of a launch runs on XCD p % n_xcd (the
     // order in which the hardware hands workgroups to the XCDs), every row
@@ -377,8 +394,9 @@ int plan_layout(const lora_table_s* t, HostPlan& p) {
     // row blocks cannot be spread evenly (the busiest XCD above 1.25 times the
     // average).  Every item still waits only on items earlier in the grid,
     // whatever the hardware does.
-    const size_t n_step = p.shrink.size() + p.reduce.size() + p.expand.size();
-    if (t->n_xcd > 1 && n_step <= (size_t)kTargetItems) {
+    p.step_len = 0;
+    p.n_xcd = t->n_xcd;
+    if (t->n_xcd > 1 && p.n_shrink + p.n_reduce + p.n_expand <= kTargetItems) {
         const int nx = t->n_xcd;
         std::vector<int> home(p.n_rb, 0), order(p.n_rb);
         for (int i = 0; i < p.n_rb; ++i) order[i] = i;
@@ -397,15 +415,21 @@ int plan_layout(const lora_table_s* t, HostPlan& p) {
             most = std::max(most, v);
         }
         if (4 * most * nx <= 5 * total) {
-            std::vector<std::vector<DevItem>> q(nx);
-            for (const auto* list : {&p.shrink, &p.reduce, &p.expand})
-                for (const DevItem& it : *list) q[home[it.rb]].push_back(it);
-            size_t len = 0;
-            for (const auto& v : q) len = std::max(len, v.size());
-            const DevItem none{};            // kind 0: does nothing
-            p.step.assign(len * nx, none);
-            for (int x = 0; x < nx; ++x)
-                for (size_t i = 0; i < q[x].size(); ++i) p.step[i * nx + x] = q[x][i];
+            // every XCD's queue: its shrink, then its reduce, then its expand items
+            std::vector<int> at(nx, 0);
+            for (int kind = 0; kind < 3; ++kind)
+                for (int i = 0; i < p.n_rb; ++i) {
+                    PlanRow& r = p.rows[i];
+                    const RowGeom q = row_geom(p.dims[r.proj()], r.rank(), r.nrows());
+                    int& u = at[home[i]];
+                    r.home = home[i];
+                    (kind == 0 ? r.step_shrink : (kind == 1 ? r.step_reduce : r.step_expand)) = u;
+                    u += kind == 0 ? q.nsplit : (kind == 1 ? (q.direct ? 0 : q.nslice) : q.ntiles);
+                }
+            for (int x = 0; x < nx; ++x) {
+                p.step_count[x] = (uint16_t)at[x];
+                p.step_len = std::max(p.step_len, at[x]);
+            }
         }
     }
 
@@ -419,15 +443,15 @@ int plan_layout(const lora_table_s* t, HostPlan& p) {
     // each, lora_shrink the fourth.
     size_t off = kHeaderBytes;                // the header (generation, status) comes first
     p.off_shrink = off;
-    off += p.shrink.size() * sizeof(DevItem);
+    off += (size_t)p.n_shrink * sizeof(DevItem);
     p.off_reduce = off;
-    off += p.reduce.size() * sizeof(DevItem);
+    off += (size_t)p.n_reduce * sizeof(DevItem);
     p.off_expand = off;
-    off += p.expand.size() * sizeof(DevItem);
+    off += (size_t)p.n_expand * sizeof(DevItem);
     p.off_reduce_all = off;
-    off += p.reduce_all.size() * sizeof(DevItem);
+    off += (size_t)p.n_all * sizeof(DevItem);
     p.off_step = off;
-    off = align_up(off + p.step.size() * sizeof(DevItem));
+    off = align_up(off + (size_t)p.step_len * p.n_xcd * sizeof(DevItem));
     p.off_perm = off;
     off = align_up(off + p.perm.size() * sizeof(int32_t));
     p.plan_bytes = off;
@@ -441,17 +465,39 @@ int plan_layout(const lora_table_s* t, HostPlan& p) {
     p.step_partials_bytes = 2 * align_up((size_t)p.n_partials * sizeof(float));   // two buffers
     p.plan_total_bytes = std::max<size_t>(off + p.step_partials_bytes, kAlign);
 
-    p.blob.assign(p.plan_bytes, 0);
-    auto put = [&](size_t at, const void* src, size_t n) {
-        if (n) std::memcpy(p.blob.data() + at, src, n);
-    };
-    put(p.off_shrink, p.shrink.data(), p.shrink.size() * sizeof(DevItem));
-    put(p.off_reduce, p.reduce.data(), p.reduce.size() * sizeof(DevItem));
-    put(p.off_expand, p.expand.data(), p.expand.size() * sizeof(DevItem));
-    put(p.off_reduce_all, p.reduce_all.data(), p.reduce_all.size() * sizeof(DevItem));
-    put(p.off_step, p.step.data(), p.step.size() * sizeof(DevItem));
-    put(p.off_perm, p.perm.data(), p.perm.size() * sizeof(int32_t));
     return LORA_OK;
+}
+
+// The items of the single launch in grid order, and lora_shrink's reduce items,
+// as lora_plan_kernel writes them.
+void list_items(const HostPlan& p, std::vector<DevItem>& grid, std::vector<DevItem>& all) {
+    grid.assign(p.n_step(), DevItem{});
+    all.assign(p.n_all, DevItem{});
+    for (int i = 0; i < p.n_rb; ++i) {
+        const PlanRow& r = p.rows[i];
+        const PlanDims& d = p.dims[r.proj()];
+        const RowGeom g = row_geom(d, r.rank(), r.nrows());
+        const DevItem base = row_item(r, g, i, p.perm.data() + r.p0);
+        auto slot = [&](int queue, int list) -> DevItem& {
+            return grid[p.step_len ? (size_t)queue * p.n_xcd + r.home : (size_t)list];
+        };
+        for (int c = 0; c < g.nsplit; ++c) {
+            DevItem it = base;
+            to_shrink(it, d, g, c);
+            slot(r.step_shrink + c, r.shrink_at + c) = it;
+        }
+        for (int c = 0; c < g.nslice; ++c) {
+            DevItem it = base;
+            to_reduce(it, g, c);
+            all[r.all_at + c] = it;
+            if (!g.direct) slot(r.step_reduce + c, p.n_shrink + r.reduce_at + c) = it;
+        }
+        for (int c = 0; c < g.ntiles; ++c) {
+            DevItem it = base;
+            to_expand(it, d, g, c);
+            slot(r.step_expand + c, p.n_shrink + p.n_reduce + r.expand_at + c) = it;
+        }
+    }
 }
 
 int build_plan(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
@@ -469,7 +515,7 @@ int build_plan_multi(const lora_table_s* const* t, int n, const lora_batch_t* b,
             return fail(LORA_E_SHAPE, "the projections differ in h_in or dtype");
         HostPlan q;
         if (int rc = plan_lists(t[c], b, q)) return rc;
-        append_lists(p, q, c);
+        if (int rc = append_lists(p, q, c)) return rc;
         p.proj_h_out.push_back(t[c]->h_out);
     }
     p.n_proj = n;
@@ -510,60 +556,83 @@ int check_compatible(const HostPlan& p, const lora_table_s* t) {
     return LORA_OK;
 }
 
-// Pinned staging ring per device for plan uploads: a slot is reused only
-// after the copy that last read it has completed.
-struct StageSlot {
-    void* host = nullptr;
-    size_t cap = 0;
-    hipEvent_t ev = nullptr;
-    bool pending = false;
-};
-constexpr int kStageSlots = 16;
-struct StageRing {
-    StageSlot slot[kStageSlots];
-    unsigned next = 0;
-};
-std::mutex g_stage_mu;
-std::vector<StageRing*> g_rings;
-
-// The calls that upload their work list through the shared ring below cannot
-// be recorded in a graph: a replay would copy whatever the ring slot holds by
-// then.  They refuse a capturing stream before enqueuing anything.
+// The calls that write a work list into device memory are not recorded in
+// graphs: a replay would write the recorded batch's again, under launches made
+// for another.  They refuse a capturing stream before enqueuing anything.
 int check_not_capturing(hipStream_t s, const char* what) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     LORA_HIP_TRY(hipStreamIsCapturing(s, &cs));
     if (cs != hipStreamCaptureStatusNone)
         return fail(LORA_E_CAPTURE, std::string(what) +
-                                        " cannot be recorded in a graph (it uploads its work list from a reused "
-                                        "host buffer); record lora_plan_apply / _shrink / _expand instead");
+                                        " cannot be recorded in a graph (it writes the work list that other "
+                                        "launches run); record lora_plan_apply / _shrink / _expand instead");
     return LORA_OK;
 }
 
-int stage_upload(int device, const void* src, size_t bytes, void* dst, hipStream_t s) {
-    if (bytes == 0) return LORA_OK;
-    std::lock_guard<std::mutex> lk(g_stage_mu);
-    if ((int)g_rings.size() <= device) g_rings.resize(device + 1, nullptr);
-    if (!g_rings[device]) g_rings[device] = new (std::nothrow) StageRing();
-    if (!g_rings[device]) return fail(LORA_E_NOMEM, "staging ring allocation failed");
-    StageRing& ring = *g_rings[device];
-    StageSlot& sl = ring.slot[ring.next++ % kStageSlots];
-    if (sl.pending) {
-        LORA_HIP_TRY(hipEventSynchronize(sl.ev));
-        sl.pending = false;
+// Write plan p's header, work list and grouped row order into the memory at w
+// (and, for a plan, clear its counters and arm its step buffers), and blob_bytes
+// (a multiple of 4) from blob to w + off_blob: as many launches as the row
+// blocks take at up to kPlanWords words each (one for about 60 row blocks).
+// No allocation, no copy engine, nothing that the host or a later call waits for.
+int write_plan(const HostPlan& p, unsigned char* w, bool arm, hipStream_t s, const void* blob = nullptr,
+               size_t blob_bytes = 0, size_t off_blob = 0) {
+    PlanArgs a{};
+    a.w = w;
+    a.off_shrink = p.off_shrink;
+    a.off_reduce = p.off_reduce;
+    a.off_expand = p.off_expand;
+    a.off_all = p.off_reduce_all;
+    a.off_step = p.off_step;
+    a.off_perm = p.off_perm;
+    a.off_sync = p.off_sync;
+    a.off_step_partials = p.off_step_partials;
+    a.pbuf = (int64_t)(p.step_partials_bytes / 2 / sizeof(float));
+    a.generation = p.generation;
+    a.arm = arm;
+    a.n_xcd = p.n_xcd;
+    a.step_len = p.step_len;
+    for (int c = 0; c < p.n_proj; ++c) a.dims[c] = p.dims[c];
+    if (p.step_len) std::memcpy(a.step_count, p.step_count, sizeof(uint16_t) * p.n_xcd);
+    size_t i = 0, blob_at = 0;
+    const size_t blob_words = blob_bytes / 4;
+    bool first = true;
+    while (first || i < p.rows.size() || blob_at < blob_words) {
+        const size_t i0 = i;
+        size_t words = 0;                     // of the row blocks and their row lists
+        for (; i < p.rows.size(); ++i) {
+            const size_t need = kRowWords + (p.rows[i].row0 < 0 ? p.rows[i].nrows() : 0);
+            if (words + need > kPlanWords) break;
+            words += need;
+        }
+        const size_t n = i - i0;
+        size_t list = n * kRowWords;
+        for (size_t j = 0; j < n; ++j) {
+            PlanRow r = p.rows[i0 + j];
+            if (r.row0 < 0) {
+                const int32_t* src = p.perm.data() + r.p0;
+                const int nb = r.nrows();
+                r.row0 = -1 - (int32_t)(list - n * kRowWords);
+                std::memcpy(a.data + list, src, sizeof(int32_t) * nb);
+                list += nb;
+            }
+            std::memcpy(a.data + j * kRowWords, &r, sizeof r);
+        }
+        a.n_rows = (int32_t)n;
+        a.row_first = (int32_t)i0;
+        a.first = first;
+        a.blob_words = 0;
+        if (i == p.rows.size() && blob_at < blob_words && words < kPlanWords) {
+            const size_t m = std::min<size_t>(kPlanWords - words, blob_words - blob_at);
+            std::memcpy(a.data + words, (const unsigned char*)blob + 4 * blob_at, 4 * m);
+            a.blob_at = (int32_t)words;
+            a.blob_words = (int32_t)m;
+            a.off_blob = off_blob + 4 * blob_at;
+            blob_at += m;
+        }
+        first = false;
+        hipLaunchKernelGGL(lora_plan_kernel, dim3((unsigned)n + 1), dim3(kThreads), 0, s, a);
+        LORA_HIP_TRY(hipGetLastError());
     }
-    if (!sl.ev) LORA_HIP_TRY(hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming));
-    if (sl.cap < bytes) {
-        if (sl.host) (void)hipHostFree(sl.host);
-        sl.host = nullptr;
-        sl.cap = 0;
-        const size_t cap = std::max<size_t>(align_up(bytes, 65536), 65536);
-        LORA_HIP_TRY(hipHostMalloc(&sl.host, cap, hipHostMallocDefault));
-        sl.cap = cap;
-    }
-    std::memcpy(sl.host, src, bytes);
-    LORA_HIP_TRY(hipMemcpyAsync(dst, sl.host, bytes, hipMemcpyHostToDevice, s));
-    LORA_HIP_TRY(hipEventRecord(sl.ev, s));
-    sl.pending = true;
     return LORA_OK;
 }
 
@@ -687,21 +756,21 @@ int enqueue(const lora_table_s* t, const HostPlan& p, unsigned char* w, const vo
     if (x) {
         KernelArgs a = make_args(t, p, w, kSpinLimit);
         a.items = (const DevItem*)(w + p.off_shrink);
-        a.n_items = (int32_t)p.shrink.size();
+        a.n_items = p.n_shrink;
         a.x = x;
         a.ldx = ldx;
         a.x_bytes = (uint32_t)span_bytes(p.n_rows, ldx, t->h_in);
         LORA_HIP_TRY(launch_shrink(a, (const uint32_t*)w, t->dtype, s));
         if (!v_out) {
             a.items = (const DevItem*)(w + p.off_reduce);
-            a.n_items = (int32_t)p.reduce.size();
+            a.n_items = p.n_reduce;
             LORA_HIP_TRY(launch_reduce(a, (const uint32_t*)w, s));
         }
     }
     if (y) {
         KernelArgs a = make_args(t, p, w, kSpinLimit);
         a.items = (const DevItem*)(w + p.off_expand);
-        a.n_items = (int32_t)p.expand.size();
+        a.n_items = p.n_expand;
         a.y = y;
         a.ldy = ldy;
         a.y_bytes = (uint32_t)span_bytes(p.n_rows, ldy, t->h_out);
@@ -718,12 +787,12 @@ int step_args(const lora_table_s* t, const HostPlan& p, unsigned char* w, const 
               int64_t ldy, int spin_limit, KernelArgs& out) {
     KernelArgs a = make_args(t, p, w, spin_limit);
     a.partials = (float*)(w + p.off_step_partials);
-    if (!p.step.empty()) {                    // the grid laid out per XCD
+    if (p.step_len) {                         // the grid laid out per XCD
         a.items = (const DevItem*)(w + p.off_step);
-        a.n_items = (int32_t)p.step.size();
+        a.n_items = p.n_step();
     } else {
         a.items = (const DevItem*)(w + p.off_shrink);
-        a.n_items = (int32_t)(p.shrink.size() + p.reduce.size() + p.expand.size());
+        a.n_items = p.n_step();
     }
     a.x = x;
     a.ldx = ldx;
@@ -737,28 +806,14 @@ int step_args(const lora_table_s* t, const HostPlan& p, unsigned char* w, const 
 
 int enqueue_step(const lora_table_s* t, const HostPlan& p, unsigned char* w, const void* x,
                  int64_t ldx, void* y, int64_t ldy, int spin_limit, hipStream_t s) {
-    KernelArgs a = make_args(t, p, w, spin_limit);
-    a.partials = (float*)(w + p.off_step_partials);
-    if (!p.step.empty()) {                    // the grid laid out per XCD
-        a.items = (const DevItem*)(w + p.off_step);
-        a.n_items = (int32_t)p.step.size();
-    } else {
-        a.items = (const DevItem*)(w + p.off_shrink);
-        a.n_items = (int32_t)(p.shrink.size() + p.reduce.size() + p.expand.size());
-    }
-    a.x = x;
-    a.ldx = ldx;
-    a.x_bytes = (uint32_t)span_bytes(p.n_rows, ldx, t->h_in);
-    a.y = y;
-    a.ldy = ldy;
-    a.y_bytes = (uint32_t)span_bytes(p.n_rows, ldy, t->h_out);
+    KernelArgs a;
+    if (int rc = step_args(t, p, w, x, ldx, y, ldy, spin_limit, a)) return rc;
     LORA_HIP_TRY(launch_step(a, (const uint32_t*)w, t->dtype, s));
     return LORA_OK;
 }
 
 // Status and row block counters to zero, both step partial buffers to the
-// sentinel (all-ones words): fill kernels, no memset.  Plan creation,
-// re-planning and the status reset.
+// sentinel (all-ones words): fill kernels, no memset.  The status reset.
 hipError_t arm_step(const HostPlan& p, unsigned char* w, hipStream_t s) {
     hipError_t e = launch_fill((uint32_t*)(w + sizeof(uint32_t)), 0u, 1, s);
     if (e == hipSuccess) e = launch_fill((uint32_t*)(w + p.off_sync), 0u, p.sync_bytes / sizeof(uint32_t), s);
@@ -781,50 +836,23 @@ struct lora_plan_s {
     unsigned char* dmem = nullptr;
     size_t capacity = 0;                // device bytes at dmem, fixed at creation
     uint32_t generation = 0;            // of the work list last uploaded
-    // two pinned staging buffers of `capacity` bytes for the uploads of
-    // lora_plan_update, used in turn; each is rewritten only after the copy
-    // that last read it has run
-    struct Stage {
-        void* host = nullptr;
-        hipEvent_t ev = nullptr;
-        bool pending = false;
-    } stage[2];
-    unsigned next_stage = 0;
 };
 
 namespace {
 
 void plan_free(lora_plan_s* pl) {
     DeviceGuard dg(pl->device);
-    for (auto& st : pl->stage) {
-        if (st.pending && st.ev) (void)hipEventSynchronize(st.ev);
-        if (st.ev) (void)hipEventDestroy(st.ev);
-        if (st.host) (void)hipHostFree(st.host);
-        st = lora_plan_s::Stage{};
-    }
     if (pl->dmem) (void)hipFree(pl->dmem);
     pl->dmem = nullptr;
     delete pl;
 }
 
-// Upload the plan's work list (header with a new generation, item lists,
-// grouped row order) from the next staging buffer and arm its step buffers,
-// all on stream s.  No allocation; the host waits only if the staging buffer
-// it takes is still being read by the copy enqueued two uploads before.
+// Write the plan's work list (header with a new generation, item lists, grouped
+// row order) and arm its step buffers, on stream s.
 int plan_upload(lora_plan_s* pl, hipStream_t s) {
     if (++pl->generation == 0) pl->generation = 1;
-    pl->plan.set_generation(pl->generation);
-    auto& st = pl->stage[pl->next_stage++ & 1u];
-    if (st.pending) {
-        LORA_HIP_TRY(hipEventSynchronize(st.ev));
-        st.pending = false;
-    }
-    std::memcpy(st.host, pl->plan.blob.data(), pl->plan.plan_bytes);
-    LORA_HIP_TRY(hipMemcpyAsync(pl->dmem, st.host, pl->plan.plan_bytes, hipMemcpyHostToDevice, s));
-    LORA_HIP_TRY(hipEventRecord(st.ev, s));
-    st.pending = true;
-    LORA_HIP_TRY(arm_step(pl->plan, pl->dmem, s));
-    return LORA_OK;
+    pl->plan.generation = pl->generation;
+    return write_plan(pl->plan, pl->dmem, true, s);
 }
 
 }  // namespace
@@ -964,14 +992,9 @@ int lora_plan_inspect(const lora_batch_t* b, int32_t h_in, int32_t h_out, int32_
     }
     HostPlan p;
     if (int rc = build_plan(&t, b, p)) return rc;
-    std::vector<const DevItem*> grid;
-    if (!p.step.empty()) {
-        for (const DevItem& it : p.step) grid.push_back(&it);
-    } else {
-        for (const auto* list : {&p.shrink, &p.reduce, &p.expand})
-            for (const DevItem& it : *list) grid.push_back(&it);
-    }
-    const size_t total = grid.size() + p.reduce_all.size();
+    std::vector<DevItem> grid, all;
+    list_items(p, grid, all);
+    const size_t total = grid.size() + all.size();
     if (total > (size_t)INT32_MAX) return fail(LORA_E_SHAPE, "plan too large to list");
     *n_items = (int32_t)total;
     if (!items) return LORA_OK;               // size query
@@ -990,8 +1013,8 @@ int lora_plan_inspect(const lora_batch_t* b, int32_t h_in, int32_t h_out, int32_
         o.grid_pos = pos;
     };
     int32_t k = 0;
-    for (size_t i = 0; i < grid.size(); ++i, ++k) put(k, *grid[i], (int32_t)i);
-    for (const DevItem& it : p.reduce_all) put(k++, it, -1);
+    for (size_t i = 0; i < grid.size(); ++i, ++k) put(k, grid[i], (int32_t)i);
+    for (const DevItem& it : all) put(k++, it, -1);
     return LORA_OK;
 }
 
@@ -1008,11 +1031,11 @@ int lora_shrink(lora_table_t t, const lora_batch_t* b, const void* x, int64_t ld
     hipStream_t s = (hipStream_t)stream;
     if (int rc = check_not_capturing(s, "lora_shrink")) return rc;
     unsigned char* w = (unsigned char*)ws;
-    if (int rc = stage_upload(t->device, p.blob.data(), p.plan_bytes, w, s)) return rc;
+    if (int rc = write_plan(p, w, false, s)) return rc;
     if (int rc = enqueue(t, p, w, x, ldx, nullptr, 0, s, true)) return rc;
     KernelArgs a = make_args(t, p, w, kSpinLimit);
     a.items = (const DevItem*)(w + p.off_reduce_all);
-    a.n_items = (int32_t)p.reduce_all.size();
+    a.n_items = p.n_all;
     a.v = v;
     a.ldv = ldv;
     LORA_HIP_TRY(launch_reduce(a, (const uint32_t*)w, s));
@@ -1032,10 +1055,10 @@ int lora_expand(lora_table_t t, const lora_batch_t* b, const float* v, int64_t l
     hipStream_t s = (hipStream_t)stream;
     if (int rc = check_not_capturing(s, "lora_expand")) return rc;
     unsigned char* w = (unsigned char*)ws;
-    if (int rc = stage_upload(t->device, p.blob.data(), p.plan_bytes, w, s)) return rc;
+    if (int rc = write_plan(p, w, false, s)) return rc;
     KernelArgs a = make_args(t, p, w, kSpinLimit);
     a.items = (const DevItem*)(w + p.off_expand);
-    a.n_items = (int32_t)p.expand.size();
+    a.n_items = p.n_expand;
     a.v = const_cast<float*>(v);
     a.ldv = ldv;
     a.y = y;
@@ -1059,7 +1082,7 @@ int lora_apply_fused(lora_table_t t, const lora_batch_t* b, const void* x, int64
     hipStream_t s = (hipStream_t)stream;
     if (int rc = check_not_capturing(s, "lora_apply_fused")) return rc;
     unsigned char* w = (unsigned char*)ws;
-    if (int rc = stage_upload(t->device, p.blob.data(), p.plan_bytes, w, s)) return rc;
+    if (int rc = write_plan(p, w, false, s)) return rc;
     return enqueue(t, p, w, x, ldx, y, ldy, s);
 }
 
@@ -1247,7 +1270,7 @@ int base_run(const lora_table_s* t, const BaseLayout& L, int n_rows, unsigned ch
         if (int rc = enqueue(t, p, w, x, ldx, nullptr, 0, s, true)) return rc;
         KernelArgs ra = make_args(t, p, w, kSpinLimit);
         ra.items = (const DevItem*)(w + p.off_reduce_all);
-        ra.n_items = (int32_t)p.reduce_all.size();
+        ra.n_items = p.n_all;
         ra.v = v;
         ra.ldv = L.ldv;
         LORA_HIP_TRY(launch_reduce(ra, (const uint32_t*)w, s));
@@ -1315,8 +1338,7 @@ int lora_base_apply(lora_table_t t, const lora_batch_t* b, const void* x, int64_
     hipStream_t s = (hipStream_t)stream;
     if (int rc = check_not_capturing(s, "lora_base_apply")) return rc;
     unsigned char* w = (unsigned char*)ws;
-    if (int rc = stage_upload(t->device, L.p.blob.data(), L.p.plan_bytes, w, s)) return rc;
-    if (int rc = stage_upload(t->device, L.pieces_blob.data(), L.pieces_blob.size(), w + L.off_pieces, s)) return rc;
+    if (int rc = write_plan(L.p, w, false, s, L.pieces_blob.data(), L.pieces_blob.size(), L.off_pieces)) return rc;
     return base_run(t, L, n_rows, w, x, ldx, wt, ldw, w_span, y, ldy, s);
 }
 
@@ -1345,11 +1367,12 @@ int lora_base_plan_create(lora_base_plan_t* out, lora_table_t t, const lora_batc
         return fail(LORA_E_NOMEM, std::string("hipMalloc of the base plan: ") + hipGetErrorString(e));
     }
     const BaseLayout& L = pl->L;
-    e = hipMemcpyAsync(pl->dmem, L.p.blob.data(), L.p.plan_bytes, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && !L.pieces_blob.empty())
-        e = hipMemcpyAsync(pl->dmem + L.off_pieces, L.pieces_blob.data(), L.pieces_blob.size(), hipMemcpyHostToDevice,
-                           s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (int rc = write_plan(L.p, pl->dmem, false, s, L.pieces_blob.data(), L.pieces_blob.size(), L.off_pieces)) {
+        (void)hipFree(pl->dmem);
+        delete pl;
+        return rc;
+    }
+    e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipFree(pl->dmem);
         delete pl;
@@ -1401,10 +1424,7 @@ int lora_apply_fused_static(lora_table_t t, const lora_batch_t* b, const void* x
     if (int rc = check_not_capturing(s, "lora_apply_fused_static")) return rc;
     unsigned char* w = nullptr;
     if (int rc = scratch_address(t->device, &w)) return rc;
-    // from pageable host memory: HIP performs this copy synchronously, so the
-    // host-side work list may go when the call returns (and the copy is
-    // ordered after the stream's earlier work, which may still read scratch)
-    LORA_HIP_TRY(hipMemcpyAsync(w, p.blob.data(), p.plan_bytes, hipMemcpyHostToDevice, s));
+    if (int rc = write_plan(p, w, false, s)) return rc;
     return enqueue(t, p, w, x, ldx, y, ldy, s);
 }
 
@@ -1452,10 +1472,6 @@ int plan_create(lora_plan_t* out, int n, const lora_table_t* tables, const lora_
     pl->capacity = align_up(std::max(pl->plan.plan_total_bytes, min_bytes));
     DeviceGuard dg(t->device);
     hipError_t e = hipMalloc((void**)&pl->dmem, pl->capacity);
-    for (auto& st : pl->stage) {
-        if (e == hipSuccess) e = hipHostMalloc(&st.host, pl->capacity, hipHostMallocDefault);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&st.ev, hipEventDisableTiming);
-    }
     if (e != hipSuccess) {
         plan_free(pl);
         return fail(LORA_E_NOMEM, std::string("plan memory: ") + hipGetErrorString(e));

@@ -1,0 +1,148 @@
+// The work list, item by item, from the row blocks: shared by the host (sizes,
+// lora_plan_inspect) and the kernel that writes the list into device memory.
+//
+// A call hands the device its row blocks (56 bytes each, and the rows of those
+// that are not consecutive) in the kernel arguments of lora_plan_kernel, which
+// expands them into the items (128 bytes each, 8 to 60 of them per block).
+// Built on the host and copied from a pinned ring, the list bounded the one-shot
+// calls: a shrink and an expand call on 1491 rows (40 blocks, 1200 items) took
+// 86 us together against 39 us now, lora_apply_fused on 203 rows 39 against 20 us,
+// an update of 48 decode rows and eight launches 128 against 103 us.
+#pragma once
+#include "lora_internal.h"
+
+namespace lora {
+
+// One projection of a plan: its shape and the two numbers that depend on the
+// whole batch.
+struct PlanDims {
+    int32_t h_in, h_out;
+    int32_t big_split;       // K ranges of row blocks of more than kInlineRows rows
+    int32_t small_step;      // 1: the step's items fit one round of workgroups
+};
+
+// One row block, as the host passes it.
+struct PlanRow {
+    int32_t group, adapter;
+    int32_t shape;           // rank | rows << 16 | projection << 24
+    int32_t p0;              // position of the first row in the grouped row order
+    int32_t row0;            // the first row when they are consecutive; else -1 - (their place in the row list)
+    uint32_t part;           // float offset of its first partial block
+    int32_t shrink_at, reduce_at, expand_at, all_at;   // its first item in each list
+    int32_t home;            // XCD, and its first items in that XCD's queue (grid laid out per XCD)
+    int32_t step_shrink, step_reduce, step_expand;
+    LORA_HD int rank() const { return shape & 0xffff; }
+    LORA_HD int nrows() const { return (shape >> 16) & 0xff; }
+    LORA_HD int proj() const { return shape >> 24; }
+};
+static_assert(sizeof(PlanRow) == 56, "PlanRow layout");
+constexpr int kRowWords = sizeof(PlanRow) / 4;
+
+// How a row block is cut into items.
+struct RowGeom {
+    int sub, krange, nsplit;      // shrink: K per pass, K per item, items
+    int nlen, ntiles;             // expand: columns per item, items
+    int pstride;                  // floats of one partial (or v) block
+    bool direct;                  // the expand items add the partial blocks up themselves
+    int slen, nslice;             // reduce: floats per item, items
+};
+
+LORA_HD inline RowGeom row_geom(const PlanDims& d, int rank, int nrows) {
+    RowGeom g;
+    g.sub = shrink_sub(rank, nrows);
+    g.krange = g.sub;
+    if (nrows > kInlineRows) {
+        const int per = (d.h_in + d.big_split - 1) / d.big_split;
+        g.krange = round_up_i(max_i(per, g.sub), g.sub);
+    }
+    g.nsplit = (d.h_in + g.krange - 1) / g.krange;
+    g.nlen = expand_nlen(rank, nrows);
+    g.ntiles = (d.h_out + g.nlen - 1) / g.nlen;
+    g.pstride = nrows * rank_stride(rank);
+    // small partial blocks of a small step are added up by the expand items themselves
+    const int64_t pbytes = (int64_t)g.nsplit * g.pstride * 4;
+    g.direct = d.small_step && g.nsplit <= kDirectSplits && pbytes <= kDirectBytes;
+    // reduce slices: at most kReduceBytes of partial values each; split groups
+    // share a float4 position (groups * positions <= threads), each thread adding
+    // at most kMaxSplitLoads blocks
+    int gmin = 1;
+    while (gmin * kMaxSplitLoads < g.nsplit) gmin *= 2;
+    const int64_t want = (pbytes + kReduceBytes - 1) / kReduceBytes;
+    const int nslice = want > 1 ? (int)want : 1;
+    g.slen = min_i(round_up_i((g.pstride + nslice - 1) / nslice, 4), 4 * (kThreads / gmin));
+    g.nslice = (g.pstride + g.slen - 1) / g.slen;
+    return g;
+}
+
+// What every item of the row block (number rb) carries; rows: its rows when they
+// are not consecutive.
+LORA_HD inline DevItem row_item(const PlanRow& r, const RowGeom& g, int rb, const int32_t* rows) {
+    DevItem it{};
+    it.part = r.part;
+    it.kind = r.proj() << kProjShift;
+    it.group = r.group;
+    it.adapter = r.adapter;
+    it.rank = r.rank();
+    it.nrows = r.nrows();
+    it.nsplit = g.nsplit;
+    it.p0 = r.p0;
+    it.pstride = g.pstride;
+    it.rb = rb;
+    it.nexp = g.ntiles;
+    it.row0 = r.row0 >= 0 ? r.row0 : -1;
+    if (it.nrows <= kInlineRows)
+        for (int i = 0; i < kInlineRows; ++i) it.rows[i] = i < it.nrows ? (r.row0 >= 0 ? r.row0 + i : rows[i]) : 0;
+    return it;
+}
+// Shrink item c: K range c of the row block.
+LORA_HD inline void to_shrink(DevItem& it, const PlanDims& d, const RowGeom& g, int c) {
+    it.kind |= kItemShrink;
+    it.part += (int64_t)c * g.pstride;
+    it.lo = c * g.krange;
+    it.len = min_i(g.krange, d.h_in - c * g.krange);
+    it.sub = shrink_uses_dma(it.rank, it.nrows) ? shrink_stage_sub(it.rank, it.nrows) : g.sub;
+}
+// Reduce item c: slice c of the row block's v.  A row block whose expand items
+// add the partial blocks up themselves adds them in order: one split group.
+LORA_HD inline void to_reduce(DevItem& it, const RowGeom& g, int c) {
+    it.kind |= kItemReduce;
+    it.lo = c * g.slen;
+    it.len = min_i(g.slen, g.pstride - c * g.slen);
+    const int np = it.len / 4;
+    int G = 1;
+    while (!g.direct && 2 * G <= g.nsplit && 2 * G * np <= kThreads) G *= 2;
+    it.sub = G;
+}
+// Expand item c: columns from c * nlen.
+LORA_HD inline void to_expand(DevItem& it, const PlanDims& d, const RowGeom& g, int c) {
+    it.kind |= kItemExpand;
+    it.sub = g.direct ? 1 : 0;
+    it.lo = c * g.nlen;
+    it.len = min_i(g.nlen, d.h_out - c * g.nlen);
+}
+
+// Arguments of lora_plan_kernel: one launch carries some of the row blocks.
+struct PlanArgs {
+    unsigned char* w;            // the plan's or workspace's memory
+    uint64_t off_shrink, off_reduce, off_expand, off_all, off_step, off_perm;
+    uint64_t off_sync, off_step_partials;
+    uint64_t off_blob;           // where the launch's extra words go
+    int64_t pbuf;                // floats from the first step buffer to the second
+    uint32_t generation;
+    int32_t arm;                 // 1: also clear the counters and arm the step buffers (plans)
+    int32_t first;               // 1: the launch that writes the header and the empty slots of the step grid
+    int32_t n_rows, row_first;   // row blocks in this launch, number of the first
+    int32_t n_xcd, step_len;     // step grid laid out per XCD: slots per XCD (0: none)
+    int32_t blob_at, blob_words; // extra words in data
+    PlanDims dims[kMaxProj];
+    uint16_t step_count[64];     // items in each XCD's queue
+    uint32_t data[912];          // row blocks, then the rows of those not consecutive, then the extra words
+};
+constexpr int kPlanWords = 912;
+static_assert(sizeof(PlanArgs) <= 4096, "kernel arguments");
+
+// One workgroup per row block: eight lanes write an item (16 bytes each).  A few
+// KB of arguments in, some hundred KB out: bounded by the launch (about 3 us).
+__global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a);
+
+}  // namespace lora
