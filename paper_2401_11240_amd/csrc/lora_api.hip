@@ -283,18 +283,31 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
     // cut into about kTargetItems / (number of such blocks) K ranges: few
     // such blocks get one pass per item (as the small blocks do), many get
     // fewer, longer items that stream their range in several passes.
-    int big_blocks = 0;
+    //
+    int big_blocks = 0, blocks = 0;
+    int64_t units = 0, small_units = 0, small_items = 0, small_bytes = 0;   // small: decode blocks that can stream
     for (int g = 0; g < p.n_groups; ++g) {
         const int r = t->host[p.group_adapter[g]].rank;
         const int rb = row_block(r);
         const int n = p.group_off[g + 1] - p.group_off[g];
-        for (int q0 = 0; q0 < n; q0 += rb)
-            if (std::min(rb, n - q0) > kInlineRows) ++big_blocks;
+        for (int q0 = 0; q0 < n; q0 += rb) {
+            const int nb = std::min(rb, n - q0);
+            units += nb + r;
+            ++blocks;
+            if (nb > kInlineRows) {
+                ++big_blocks;
+            } else if (shrink_can_dma(r, nb)) {
+                small_units += nb + r;
+                small_items += (t->h_in + shrink_sub(r, nb) - 1) / shrink_sub(r, nb);
+                small_bytes += (int64_t)r * t->h_in * 2;
+            }
+        }
     }
     PlanDims& d = p.dims[0];
     d.h_in = t->h_in;
     d.h_out = t->h_out;
     d.big_split = big_blocks ? std::max(1, (kTargetItems + big_blocks - 1) / big_blocks) : 1;
+    d.units = d.items = 0;
     d.small_step = 0;
     // A step whose shrink and expand items fit one round of workgroups
     // (decode) lets expand items add small partial blocks themselves, one hop
@@ -312,6 +325,26 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
         }
     }
     d.small_step = step_items <= kTargetItems;
+    // Steps whose decode blocks alone would take a round or more of one-pass
+    // shrink items of 16 KiB and up, and that prompt blocks do not dominate, have
+    // all blocks cut by bytes into about one round (one and a half where an item
+    // would pass 64 KiB), a decode block's range streaming in several passes: an
+    // item's fixed part (launch, work item, pointer: about half of its 7 us at one
+    // pass of 32 KiB) is then paid once per range.  Measured per launch, one pass
+    // per decode item against ranges: 70B-shaped q and gate (256 tokens, 4 prompts
+    // of 512) 283 -> 251 us (in 512, 1024, 1536 items 246, 257, 266), 65 adapters of
+    // rank 16 at 5120 -> 2768 16.2 -> 13.8; 57 tokens of rank 8-128 at 8192 -> 3872
+    // 28.1 -> 28.2 (in 512 items 29.2).  Past the lines it turns: 131 tokens at 9264
+    // -> 13824 (485 decode items, one round anyway) 29.0 -> 30.6, 43 tokens of rank 8
+    // at 12120 11.9 -> 13.0, 25 adapters beside 12 prompts of up to 364 tokens 49.5 ->
+    // 55.4 us.  (The cut depends on one projection only: a launch of several equals
+    // one launch each, bit for bit.)
+    if (!d.small_step && small_items >= kTargetItems && small_bytes >= (small_items << 14) &&
+        3 * small_units >= units && units <= INT32_MAX) {
+        const bool wide = units * t->h_in * 2 >= (int64_t)kTargetItems << 16;
+        d.units = (int32_t)units;
+        d.items = std::max(wide ? 3 * kTargetItems / 2 : kTargetItems, blocks);
+    }
 
     for (int g = 0; g < p.n_groups; ++g) {
         const int r = t->host[p.group_adapter[g]].rank;
@@ -321,7 +354,7 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
         for (int p0 = p.group_off[g]; p0 < p.group_off[g + 1]; p0 += rb) {
             const int nb = std::min(rb, p.group_off[g + 1] - p0);
             const RowGeom q = row_geom(d, r, nb);
-            if ((!shrink_uses_dma(r, nb) && shrink_lds_bytes(r, q.sub, nb) > kShrinkLds) || !expand_fits_lds(r, nb))
+            if (shrink_lds_bytes(r, q.sub, nb) > kShrinkLds || !expand_fits_lds(r, nb))
                 return fail(LORA_E_SHAPE, "internal: a tile exceeds LDS");
             PlanRow row{};
             row.group = g;
@@ -677,6 +710,7 @@ KernelArgs make_args(const lora_table_s* t, const HostPlan& p, unsigned char* w,
     a.h_in = t->h_in;
     a.h_out = t->h_out;
     a.n_groups = p.n_groups;
+    for (int c = 0; c < p.n_proj; ++c) a.streams |= p.dims[c].items > 0;
     const int ng = std::min(p.n_groups, kKargGroups);
     for (int g = 0; g < ng; ++g) {
         const DevAdapter& ad = t->host[p.group_adapter[g]];
@@ -1007,7 +1041,7 @@ int lora_plan_inspect(const lora_batch_t* b, int32_t h_in, int32_t h_out, int32_
         o.nrows = it.nrows;
         o.lo = it.lo;
         o.len = it.len;
-        o.sub = it.sub;
+        o.sub = it.sub & (kSubDma - 1);
         o.nsplit = it.nsplit;
         o.pstride = it.pstride;
         o.grid_pos = pos;

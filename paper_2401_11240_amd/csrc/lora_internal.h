@@ -96,7 +96,8 @@ struct DevAdapter {
 static_assert(sizeof(DevAdapter) == 32, "DevAdapter layout");
 
 // One work item = one workgroup (128 bytes, read with scalar loads).
-//   shrink: part = its partial block; lo, len = K range; sub = K per pass
+//   shrink: part = its partial block; lo, len = K range; sub = K per pass,
+//           with kSubDma set for a decode block whose range has several passes
 //   reduce: part = first partial block of the row block (the v block follows
 //           the nsplit partial blocks); lo = first float of the slice, len =
 //           its floats (multiple of 4); sub = split groups (see reduce_body)
@@ -124,6 +125,7 @@ struct DevItem {
 };
 static_assert(sizeof(DevItem) == 128, "DevItem layout");
 
+constexpr int kSubDma = 1 << 16;
 constexpr int kMaxProj = 4;       // projections one launch may carry (q, k, v; gate, up)
 constexpr int kProjShift = 8;     // DevItem::kind holds the projection above this bit
 
@@ -149,6 +151,7 @@ struct KernelArgs {
     uint32_t x_bytes;           // bytes from x to the end of its last row (< 2 GiB)
     uint32_t y_bytes;           // bytes from y to the end of its last row (< 2 GiB)
     uint32_t generation;        // the work list these arguments were made for (header word 0)
+    int32_t streams;            // 1: decode blocks may have ranges of several passes (kSubDma)
     int32_t n_proj;             // projections sharing x in this launch (items carry their projection)
     const void* gfac[2 * kKargGroups];   // per group g: [2g] = A_g, [2g + 1] = B_g
     float gscale[kKargGroups];           // per group: s_g
@@ -230,19 +233,19 @@ LORA_HD inline int row_block(int rank) { return round_up_i(rank, 16) > 128 ? 32 
 // byte reads and writes of eight consecutive lanes hit distinct banks).
 LORA_HD inline int shrink_chunks(int sub) { return sub / 8 + 1; }
 // Waves side by side over rank tiles (1, 2 or 4); the others split K.  Items
-// of one 16-row subtile (decode) never split K: their MFMA work is a few
-// hundred cycles, less than adding wave sums through LDS would cost.
-LORA_HD inline int shrink_wn(int rank, int nrows) {
+// of one pass over one 16-row subtile (decode) never split K: their MFMA work
+// is a few hundred cycles, less than adding wave sums through LDS would cost.
+LORA_HD inline int shrink_wn_split(int rank) {
     const int nt = round_up_i(rank, 16) / 16;
-    if (msub_body(nrows) == 1) return 4;
     return nt >= 4 ? 4 : (nt >= 2 ? 2 : 1);
 }
-LORA_HD inline int shrink_tq(int rank, int nrows) {     // rank tiles per wave: 1, 2 or 4
+LORA_HD inline int shrink_wn(int rank, int nrows) { return msub_body(nrows) == 1 ? 4 : shrink_wn_split(rank); }
+LORA_HD inline int shrink_tq_of(int rank, int wn) {     // rank tiles per wave: 1, 2 or 4
     const int nt = round_up_i(rank, 16) / 16;
-    const int wn = shrink_wn(rank, nrows);
     const int q = (nt + wn - 1) / wn;
     return q <= 1 ? 1 : (q <= 2 ? 2 : 4);
 }
+LORA_HD inline int shrink_tq(int rank, int nrows) { return shrink_tq_of(rank, shrink_wn(rank, nrows)); }
 LORA_HD inline int shrink_lds_bytes(int rank, int sub, int nrows) {
     const int rp = round_up_i(rank, 16);
     const int staged = (rp + msub_body(nrows) * 16) * shrink_chunks(sub) * 16;
@@ -277,9 +280,11 @@ LORA_HD inline int shrink_stage_sub(int rank, int nrows) {
         if (round_up_i(k * (rank / 8), 64) + 2 * ms * k <= kStageChunks) return k;
     return 0;
 }
-// Only row blocks of more than one 16-row subtile stream through the LDS
-// buffers; a decode block's pass is one memory round trip either way, and the
-// register-staged body measured faster there.
+LORA_HD inline bool shrink_can_dma(int rank, int nrows) { return shrink_stage_sub(rank, nrows) >= 32; }
+// Row blocks of more than one 16-row subtile stream through the LDS buffers;
+// for a decode block's one pass, one memory round trip either way, the
+// register-staged body measured faster (decode step 12.3 against 13.7 us).
+// Decode blocks with ranges of several passes (kSubDma) stream too.
 LORA_HD inline bool shrink_uses_dma(int rank, int nrows) {
     return msub_body(nrows) > 1 && shrink_stage_sub(rank, nrows) >= 32;
 }

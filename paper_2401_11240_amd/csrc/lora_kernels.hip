@@ -583,7 +583,7 @@ __device__ __forceinline__ void shrink_dma_body(const KernelArgs& a, const Item&
     const int nAr = round_up_i(nA, 64);
     const int nX = MS * 16 * cpx;
     const int nrows = it.nrows;
-    const int WN = shrink_wn(R, nrows);
+    const int WN = shrink_wn_split(R);
     const int WK = 4 / WN;
     const int wn = w % WN;
     const int wk = w / WN;
@@ -773,10 +773,23 @@ __device__ __forceinline__ void shrink_dma_body(const KernelArgs& a, const Item&
     }
 }
 
-template <class Fmt, bool kSync>
-__device__ __forceinline__ void shrink_item(const KernelArgs& a, const Item& it, unsigned char* smem) {
+// kStream: launches whose decode blocks may have ranges of several passes.  A
+// variant of its own: with the bodies for those in every kernel, launches that
+// have none took 3-6% longer.
+template <class Fmt, bool kSync, bool kStream = false>
+__device__ __forceinline__ void shrink_item(const KernelArgs& a, Item& it, unsigned char* smem) {
     const int tq = shrink_tq(it.rank, it.nrows);
     const int ms = msub_body(it.nrows);
+    if constexpr (kStream) {
+        if (it.sub & kSubDma) {               // ms is 1
+            it.sub &= kSubDma - 1;
+            const int tqs = shrink_tq_of(it.rank, shrink_wn_split(it.rank));   // its waves may split K
+            if (tqs == 1) shrink_dma_body<Fmt, 1, 1, kSync>(a, it, smem);
+            else if (tqs == 2) shrink_dma_body<Fmt, 2, 1, kSync>(a, it, smem);
+            else shrink_dma_body<Fmt, 4, 1, kSync>(a, it, smem);
+            return;
+        }
+    }
     if (shrink_uses_dma(it.rank, it.nrows)) {     // ms is 2 or 4
         if (tq == 1) {
             if (ms == 2) shrink_dma_body<Fmt, 1, 2, kSync>(a, it, smem);
@@ -805,13 +818,13 @@ __device__ __forceinline__ void shrink_item(const KernelArgs& a, const Item& it,
     }
 }
 
-template <class Fmt>
+template <class Fmt, bool kStream>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) lora_shrink_kernel(const DevItem* __restrict__ items, const uint32_t* __restrict__ hdr, KernelArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[kShrinkLds];
     Item it = load_item(items + blockIdx.x);
     if (stale(hdr, a) || it.kind != kItemShrink) return;
     resolve<kLookupAuto>(a, it);
-    shrink_item<Fmt, false>(a, it, smem);
+    shrink_item<Fmt, false, kStream>(a, it, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1285,7 +1298,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 // a kernel argument of its own, ahead of the argument block, so that it can
 // be preloaded into scalar registers at wave launch.
 // ---------------------------------------------------------------------------
-template <class Fmt, int kLookup>
+template <class Fmt, int kLookup, bool kStream>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 lora_step_kernel(const DevItem* __restrict__ items, const uint32_t* __restrict__ hdr, KernelArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[kStepLds];
@@ -1301,7 +1314,7 @@ lora_step_kernel(const DevItem* __restrict__ items, const uint32_t* __restrict__
         if (it.kind == kItemShrink || it.kind == kItemExpand) resolve<kLookup>(a, it);
     }
     constexpr bool kMulti = kLookup == kLookupMulti;
-    if (it.kind == kItemShrink) shrink_item<Fmt, true>(a, it, smem);
+    if (it.kind == kItemShrink) shrink_item<Fmt, true, kStream>(a, it, smem);
     else if (it.kind == kItemExpand) expand_item<Fmt, true, kMulti>(a, it, smem);
     else if (it.kind == kItemReduce) reduce_body<true>(a, it, smem);
 }
@@ -1311,10 +1324,9 @@ lora_step_kernel(const DevItem* __restrict__ items, const uint32_t* __restrict__
 // ---------------------------------------------------------------------------
 hipError_t launch_shrink(const KernelArgs& a, const uint32_t* hdr, int dtype, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
-    if (dtype == 0)
-        hipLaunchKernelGGL(lora_shrink_kernel<FmtF16>, dim3(a.n_items), dim3(kThreads), 0, s, a.items, hdr, a);
-    else
-        hipLaunchKernelGGL(lora_shrink_kernel<FmtBF16>, dim3(a.n_items), dim3(kThreads), 0, s, a.items, hdr, a);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.n_items), dim3(kThreads), 0, s, a.items, hdr, a); };
+    if (dtype == 0) a.streams ? go(lora_shrink_kernel<FmtF16, true>) : go(lora_shrink_kernel<FmtF16, false>);
+    else a.streams ? go(lora_shrink_kernel<FmtBF16, true>) : go(lora_shrink_kernel<FmtBF16, false>);
     return hipGetLastError();
 }
 
@@ -1329,18 +1341,22 @@ hipError_t launch_expand(const KernelArgs& a, const uint32_t* hdr, int dtype, hi
 
 hipError_t launch_step(const KernelArgs& a, const uint32_t* hdr, int dtype, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
-    const dim3 g(a.n_items), b(kThreads);
-    const bool args = a.n_groups <= kKargGroups;
-    if (a.n_proj > 1) {
-        if (dtype == 0) hipLaunchKernelGGL((lora_step_kernel<FmtF16, kLookupMulti>), g, b, 0, s, a.items, hdr, a);
-        else hipLaunchKernelGGL((lora_step_kernel<FmtBF16, kLookupMulti>), g, b, 0, s, a.items, hdr, a);
-    } else if (dtype == 0) {
-        if (args) hipLaunchKernelGGL((lora_step_kernel<FmtF16, kLookupArgs>), g, b, 0, s, a.items, hdr, a);
-        else hipLaunchKernelGGL((lora_step_kernel<FmtF16, kLookupReg>), g, b, 0, s, a.items, hdr, a);
-    } else {
-        if (args) hipLaunchKernelGGL((lora_step_kernel<FmtBF16, kLookupArgs>), g, b, 0, s, a.items, hdr, a);
-        else hipLaunchKernelGGL((lora_step_kernel<FmtBF16, kLookupReg>), g, b, 0, s, a.items, hdr, a);
-    }
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.n_items), dim3(kThreads), 0, s, a.items, hdr, a); };
+    auto pick = [&](auto fmt) {
+        using Fmt = decltype(fmt);
+        if (a.n_proj > 1) {
+            if (a.streams) go(lora_step_kernel<Fmt, kLookupMulti, true>);
+            else go(lora_step_kernel<Fmt, kLookupMulti, false>);
+        } else if (a.streams) {               // large steps: the registry, for any number of groups
+            go(lora_step_kernel<Fmt, kLookupReg, true>);
+        } else if (a.n_groups <= kKargGroups) {
+            go(lora_step_kernel<Fmt, kLookupArgs, false>);
+        } else {
+            go(lora_step_kernel<Fmt, kLookupReg, false>);
+        }
+    };
+    if (dtype == 0) pick(FmtF16{});
+    else pick(FmtBF16{});
     return hipGetLastError();
 }
 

@@ -18,6 +18,8 @@ namespace lora {
 struct PlanDims {
     int32_t h_in, h_out;
     int32_t big_split;       // K ranges of row blocks of more than kInlineRows rows
+    int32_t units, items;    // large decode steps (items > 0): all row blocks share so many shrink items by
+                             // their bytes, rows + rank each (units: their sum)
     int32_t small_step;      // 1: the step's items fit one round of workgroups
 };
 
@@ -51,7 +53,11 @@ LORA_HD inline RowGeom row_geom(const PlanDims& d, int rank, int nrows) {
     RowGeom g;
     g.sub = shrink_sub(rank, nrows);
     g.krange = g.sub;
-    if (nrows > kInlineRows) {
+    if (d.items > 0 && (nrows > kInlineRows || shrink_can_dma(rank, nrows))) {
+        const int n = (int)((int64_t)(nrows + rank) * d.items / d.units);
+        const int per = n > 1 ? (d.h_in + n - 1) / n : d.h_in;
+        g.krange = round_up_i(max_i(per, g.sub), g.sub);
+    } else if (nrows > kInlineRows) {
         const int per = (d.h_in + d.big_split - 1) / d.big_split;
         g.krange = round_up_i(max_i(per, g.sub), g.sub);
     }
@@ -100,7 +106,10 @@ LORA_HD inline void to_shrink(DevItem& it, const PlanDims& d, const RowGeom& g, 
     it.part += (int64_t)c * g.pstride;
     it.lo = c * g.krange;
     it.len = min_i(g.krange, d.h_in - c * g.krange);
-    it.sub = shrink_uses_dma(it.rank, it.nrows) ? shrink_stage_sub(it.rank, it.nrows) : g.sub;
+    if (shrink_uses_dma(it.rank, it.nrows)) it.sub = shrink_stage_sub(it.rank, it.nrows);
+    else if (d.items > 0 && it.len > g.sub && shrink_can_dma(it.rank, it.nrows))
+        it.sub = shrink_stage_sub(it.rank, it.nrows) | kSubDma;
+    else it.sub = g.sub;
 }
 // Reduce item c: slice c of the row block's v.  A row block whose expand items
 // add the partial blocks up themselves adds them in order: one split group.
