@@ -1,9 +1,10 @@
 // Internal layout shared by the host planner and the gfx950 kernels.
 //
-// A step is planned on the host into flat lists of work items, one per
-// workgroup.  Rows are first grouped by adapter (the per-token gather of
-// Sections 2.3 C2 / 4.1) and each group is cut into row blocks of at most
-// 64 rows.  Each row block then becomes three kinds of items:
+// A step is planned on the host into row blocks, which a kernel expands into
+// flat lists of work items, one per workgroup (lora_plan.h).  Rows are first
+// grouped by adapter (the per-token gather of Sections 2.3 C2 / 4.1) and each
+// group is cut into row blocks of at most 64 rows.  Each row block then
+// becomes three kinds of items:
 //
 //   shrink  (row block, K range of A_g): a float32 partial block
 //           P_c[row, 0:Rv] = sum over the K range of x[row, k] A_g[k, :];
