@@ -61,6 +61,10 @@ LORA_HD inline RowGeom row_geom(const PlanDims& d, int rank, int nrows) {
         const int per = (d.h_in + d.big_split - 1) / d.big_split;
         g.krange = round_up_i(max_i(per, g.sub), g.sub);
     }
+    // more ranges than the reduction can add up (h_in past 256 Ki at rank 256, 2 Mi at
+    // rank 8): longer ones, of several passes
+    if ((int64_t)g.krange * kMaxRanges < d.h_in)
+        g.krange = round_up_i((d.h_in + kMaxRanges - 1) / kMaxRanges, g.sub);
     g.nsplit = (d.h_in + g.krange - 1) / g.krange;
     g.nlen = expand_nlen(rank, nrows);
     g.ntiles = (d.h_out + g.nlen - 1) / g.nlen;
@@ -70,7 +74,7 @@ LORA_HD inline RowGeom row_geom(const PlanDims& d, int rank, int nrows) {
     g.direct = d.small_step && g.nsplit <= kDirectSplits && pbytes <= kDirectBytes;
     // reduce slices: at most kReduceBytes of partial values each; split groups
     // share a float4 position (groups * positions <= threads), each thread adding
-    // at most kMaxSplitLoads blocks
+    // at most kMaxSplitLoads blocks (gmin <= kThreads, as nsplit <= kMaxRanges)
     int gmin = 1;
     while (gmin * kMaxSplitLoads < g.nsplit) gmin *= 2;
     const int64_t want = (pbytes + kReduceBytes - 1) / kReduceBytes;

@@ -166,6 +166,31 @@ void check_plan(const Batch& b, int n_adapters) {
     (void)grid_items;
 }
 
+// h_in to the largest accepted: K covered once, and no more ranges than a reduce
+// item's split groups add up at 16 each
+void check_long_plans() {
+    for (int h_in : {262144, 262152, 1 << 20, 2097152, 2097160, 4194176})
+        for (int rank : {1, 8, 12, 16, 200, 256})
+            for (int rows : {1, 16, 17, 64}) {
+                const int32_t so[] = {0, rows}, sa[] = {0}, r[] = {rank};
+                const lora_batch_t b{rows, 1, so, sa};
+                int32_t n = 0;
+                int rc = lora_plan_inspect(&b, h_in, 64, 1, r, 8, nullptr, 0, &n);
+                CHECK(rc == LORA_OK || (rc == LORA_E_SHAPE && n == 0), "h_in %d rank %d rows %d: rc %d", h_in, rank, rows, rc);
+                if (rc != LORA_OK) continue;
+                std::vector<lora_item_info_t> it(n);
+                rc = lora_plan_inspect(&b, h_in, 64, 1, r, 8, it.data(), n, &n);
+                CHECK(rc == LORA_OK, "inspect rc %d", rc);
+                std::vector<int64_t> k(64, 0);
+                for (const auto& q : it) {
+                    if (q.kind == 1) k[q.row_block] += q.len;
+                    if (q.kind == 3) CHECK(16 * q.sub >= q.nsplit, "h_in %d rank %d: %d blocks in %d groups", h_in, rank, q.nsplit, q.sub);
+                }
+                for (const auto& q : it)
+                    if (q.kind == 1) CHECK(k[q.row_block] == h_in, "h_in %d rank %d rows %d: K %lld", h_in, rank, rows, (long long)k[q.row_block]);
+            }
+}
+
 void check_errors(int n_adapters) {
     std::vector<int32_t> perm(16), off(17), ad(16);
     int32_t G = 0;
@@ -344,6 +369,7 @@ int main() {
         check_grouping(b, n_adapters);
         check_plan(b, n_adapters);
     }
+    check_long_plans();
     check_errors(7);
     check_oracle();
     check_sched(200);

@@ -77,3 +77,34 @@ def test_streamed_ranges(dtype, h_in, rows):
             assert np.array_equal(D.from_device_bits(y), ref)
     L.lora_plan_destroy(plan)
     dw.release()
+
+
+@pytest.mark.parametrize("dtype,ranks", [(W.F16, [8, 12, 8]), (W.BF16, [32, 12, 24])])
+def test_long_contraction(dtype, ranks):
+    """h_in past what 4096 one-pass K ranges cover: ranges of several passes in
+    every body (the token of rank 32 streams, those of rank 8 and 12 go through
+    registers)."""
+    h_in = 4096 * 512 + 8
+    print("long contraction", dtype, ranks, flush=True)
+    w = W.build_workload(name="long", seed=5, dtype=dtype, n_adapters=3, fixed_ranks=ranks, seg_adapter=[0, 1, 2],
+                         seg_lens=[1, 1, 18], projections=(("proj", h_in, 264, "x"),))
+    items = L.lora_plan_inspect(L.Batch(w.seg_offset, w.seg_adapter), h_in, 264, w.ranks, 8)
+    sh = items[(items["kind"] == 1) & (items["nrows"] == 1)]
+    assert items["nsplit"].max() <= 4096 and np.unique(sh["rank"][sh["len"] > 512]).size == 2
+    dw = D.upload(w, DEV)
+    p, pr = dw.projections[0], w.projections[0]
+    s = torch.cuda.current_stream(DEV)
+    plan = L.lora_plan_create(p.table, dw.batch, s)
+    y = p.y.clone()
+    L.lora_plan_apply(plan, p.table, dw.xs["x"], h_in, y, p.h_out, s)
+    L.lora_plan_status(plan, s)
+    got = D.from_device_bits(y)
+    ref = oracle.lora_apply(w.seg_offset, w.seg_adapter, w.xs["x"], pr.A, pr.B, w.ranks, w.scales, pr.y, w.dtype)
+    compare(got, ref, w.dtype, "long contraction", mag=magnitude(w, pr.name))
+    y2 = p.y.clone()
+    L.lora_plan_shrink(plan, p.table, dw.xs["x"], h_in, s)
+    L.lora_plan_expand(plan, p.table, y2, p.h_out, s)
+    torch.cuda.synchronize()
+    assert np.array_equal(D.from_device_bits(y2), got)
+    L.lora_plan_destroy(plan)
+    dw.release()

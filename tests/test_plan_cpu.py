@@ -100,6 +100,8 @@ def check_plan(items, h_in, h_out, n_xcd):
         assert np.all(ex["len"] % 8 == 0)
         check_lds_fit(rank, nrows, sh, ex)
         assert partitions(zip(allrd["lo"], allrd["len"]), pstride)
+        for r in (allrd, rd):                  # 256 threads: a position's split groups, each adding at most 16 blocks
+            assert np.all(16 * r["sub"] >= nsplit) and np.all(r["sub"] * (r["len"] // 4) <= 256)
         direct = set(ex["sub"].tolist())
         assert len(direct) == 1
         if direct == {1}:
@@ -148,6 +150,18 @@ def test_random_plans(seed):
         for it in grid:
             blocks[int(it["row_block"])] = int(it["nrows"])
         assert sum(blocks.values()) == adapted
+
+
+@pytest.mark.parametrize("h_in", [262144, 262152, 2097152, 2097160, 4194176])
+@pytest.mark.parametrize("ranks", [[256], [8], [12, 1], [16, 24]])
+def test_long_contractions(h_in, ranks):
+    """h_in around and past what 4096 one-pass K ranges cover (the most that one
+    reduction adds up), to the largest accepted; one token per adapter, and a prompt."""
+    lens = [1] * len(ranks) + [17]
+    b = L.Batch(np.concatenate([[0], np.cumsum(lens)]), list(range(len(ranks))) + [0])
+    items = L.lora_plan_inspect(b, h_in, 264, ranks, n_xcd=8)
+    check_plan(items, h_in, 264, 8)
+    assert items["nsplit"].max() <= 4096
 
 
 def test_decode_headline_is_laid_out_and_few_adapters_are_not():
