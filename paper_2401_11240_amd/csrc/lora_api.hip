@@ -201,6 +201,13 @@ struct HostPlan {
     uint16_t step_count[64];            // items in each XCD's queue
     int n_rows = 0;
     int64_t n_partials = 0;
+    // The same of the plan without ranges cut by bytes: what it is sized for.
+    // A part of a batch may fall below the line from which they are cut, and
+    // has to fit where the whole batch did.
+    struct Counts {
+        int64_t shrink = 0, reduce = 0, all = 0, partials = 0;
+    } uncut;
+    size_t uncut_bytes = 0, uncut_total_bytes = 0;   // total_bytes and plan_total_bytes of that plan
     size_t off_shrink = 0, off_expand = 0, off_reduce = 0, off_reduce_all = 0, off_step = 0, off_perm = 0;
     size_t plan_bytes = 0, off_partials = 0, off_sync = 0, sync_bytes = 0, total_bytes = 0;
     size_t off_step_partials = 0, step_partials_bytes = 0, plan_total_bytes = 0;
@@ -277,6 +284,7 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
     p.rb_bytes.clear();
     p.n_proj = 1;
     p.n_partials = 0;
+    p.uncut = {};
     p.n_shrink = p.n_reduce = p.n_expand = p.n_all = 0;
 
     // Row blocks of more than 16 rows (prompt segments, popular adapters) are
@@ -322,8 +330,12 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
         for (int q0 = 0; q0 < n; q0 += rb) {
             const RowGeom q = row_geom(d, r, std::min(rb, n - q0));
             step_items += q.nsplit + q.ntiles;
+            p.uncut.shrink += q.nsplit;
+            p.uncut.reduce += q.nslice;
+            p.uncut.partials += (int64_t)(q.nsplit + 1) * q.pstride;
         }
     }
+    p.uncut.all = p.uncut.reduce;
     d.small_step = step_items <= kTargetItems;
     // Steps whose decode blocks alone would take a round or more of one-pass
     // shrink items of 16 KiB and up, and that prompt blocks do not dominate, have
@@ -381,6 +393,7 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
         }
     }
     p.n_rb = (int)p.rows.size();
+    if (d.items == 0) p.uncut = {p.n_shrink, p.n_reduce, p.n_all, p.n_partials};
     return LORA_OK;
 }
 
@@ -408,6 +421,10 @@ int append_lists(HostPlan& p, const HostPlan& q, int c) {
     p.rb_bytes.insert(p.rb_bytes.end(), q.rb_bytes.begin(), q.rb_bytes.end());
     p.n_partials += q.n_partials;
     p.n_rb += q.n_rb;
+    p.uncut.shrink += q.uncut.shrink;
+    p.uncut.reduce += q.uncut.reduce;
+    p.uncut.all += q.uncut.all;
+    p.uncut.partials += q.uncut.partials;
     return LORA_OK;
 }
 
@@ -429,7 +446,7 @@ int plan_layout(const lora_table_s* t, HostPlan& p) {
     // whatever the hardware does.
     p.step_len = 0;
     p.n_xcd = t->n_xcd;
-    if (t->n_xcd > 1 && p.n_shrink + p.n_reduce + p.n_expand <= kTargetItems) {
+    if (t->n_xcd > 1 && p.uncut.shrink + p.uncut.reduce + p.n_expand <= kTargetItems) {
         const int nx = t->n_xcd;
         std::vector<int> home(p.n_rb, 0), order(p.n_rb);
         for (int i = 0; i < p.n_rb; ++i) order[i] = i;
@@ -498,6 +515,13 @@ int plan_layout(const lora_table_s* t, HostPlan& p) {
     p.step_partials_bytes = 2 * align_up((size_t)p.n_partials * sizeof(float));   // two buffers
     p.plan_total_bytes = std::max<size_t>(off + p.step_partials_bytes, kAlign);
 
+    // the same sizes without ranges cut by bytes
+    const size_t items = (size_t)(p.uncut.shrink + p.uncut.reduce + p.n_expand + p.uncut.all) + (size_t)p.step_len * p.n_xcd;
+    off = align_up(kHeaderBytes + items * sizeof(DevItem));
+    off = align_up(off + p.perm.size() * sizeof(int32_t));
+    off = align_up(off + (size_t)p.uncut.partials * sizeof(float)) + p.sync_bytes;
+    p.uncut_bytes = std::max<size_t>(off, kAlign);
+    p.uncut_total_bytes = std::max<size_t>(off + 2 * align_up((size_t)p.uncut.partials * sizeof(float)), kAlign);
     return LORA_OK;
 }
 
@@ -982,7 +1006,7 @@ int lora_workspace_bytes(lora_table_t t, const lora_batch_t* b, size_t* bytes) {
     if (!bytes) return fail(LORA_E_ARG, "bytes is NULL");
     HostPlan p;
     if (int rc = build_plan(t, b, p)) return rc;
-    *bytes = p.total_bytes;
+    *bytes = p.uncut_bytes;
     return LORA_OK;
 }
 
@@ -1167,7 +1191,7 @@ void choose_split(int n_tiles, int h_in, int n_cu, BaseLayout& L) {
 int build_base(const lora_table_s* t, const lora_batch_t* b, BaseLayout& L) {
     if (int rc = build_plan(t, b, L.p)) return rc;
     L.ldv = round_up_i(std::max(L.p.r_max, 1), 8);
-    L.off_v = align_up(L.p.total_bytes);
+    L.off_v = align_up(L.p.uncut_bytes);
     L.v_bytes = (size_t)b->n_rows * L.ldv * sizeof(float);
     if (L.v_bytes > kMaxSpan) return fail(LORA_E_SHAPE, "batch too large: its float32 intermediate exceeds 2 GiB");
     // the big tile while its whole tiles fill the compute units; else the
@@ -1467,7 +1491,7 @@ int lora_plan_bytes(lora_table_t t, const lora_batch_t* b, size_t* bytes) {
     if (!bytes) return fail(LORA_E_ARG, "bytes is NULL");
     HostPlan p;
     if (int rc = build_plan(t, b, p)) return rc;
-    *bytes = p.plan_total_bytes;
+    *bytes = p.uncut_total_bytes;
     return LORA_OK;
 }
 
@@ -1503,7 +1527,7 @@ int plan_create(lora_plan_t* out, int n, const lora_table_t* tables, const lora_
             return rc;
         }
     pl->n_rows = b->n_rows;
-    pl->capacity = align_up(std::max(pl->plan.plan_total_bytes, min_bytes));
+    pl->capacity = align_up(std::max(pl->plan.uncut_total_bytes, min_bytes));
     DeviceGuard dg(t->device);
     hipError_t e = hipMalloc((void**)&pl->dmem, pl->capacity);
     if (e != hipSuccess) {

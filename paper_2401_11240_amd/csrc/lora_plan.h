@@ -53,13 +53,16 @@ LORA_HD inline RowGeom row_geom(const PlanDims& d, int rank, int nrows) {
     RowGeom g;
     g.sub = shrink_sub(rank, nrows);
     g.krange = g.sub;
+    if (nrows > kInlineRows) {
+        const int per = (d.h_in + d.big_split - 1) / d.big_split;
+        g.krange = round_up_i(max_i(per, g.sub), g.sub);
+    }
+    // (never more ranges than without the cut by bytes, so that a step it is taken
+    // for needs no more memory: a plan or workspace that holds a batch holds its parts)
     if (d.items > 0 && (nrows > kInlineRows || shrink_can_dma(rank, nrows))) {
         const int n = (int)((int64_t)(nrows + rank) * d.items / d.units);
         const int per = n > 1 ? (d.h_in + n - 1) / n : d.h_in;
-        g.krange = round_up_i(max_i(per, g.sub), g.sub);
-    } else if (nrows > kInlineRows) {
-        const int per = (d.h_in + d.big_split - 1) / d.big_split;
-        g.krange = round_up_i(max_i(per, g.sub), g.sub);
+        g.krange = max_i(g.krange, round_up_i(per, g.sub));
     }
     // more ranges than the reduction can add up (h_in past 256 Ki at rank 256, 2 Mi at
     // rank 8): longer ones, of several passes

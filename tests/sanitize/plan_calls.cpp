@@ -1,0 +1,104 @@
+// The host side of the plan and one-shot calls against a stand-in HIP runtime:
+// device memory is host memory, launches are recorded and not run.  Built with
+// AddressSanitizer and UndefinedBehaviorSanitizer on the host code; no GPU.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <numeric>
+#include <vector>
+
+#include <hip/hip_runtime.h>
+
+#include "lora.h"
+#include "lora_internal.h"
+
+namespace lora {
+hipError_t launch_shrink(const KernelArgs&, const uint32_t*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_expand(const KernelArgs&, const uint32_t*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_reduce(const KernelArgs&, const uint32_t*, hipStream_t) { return hipSuccess; }
+hipError_t launch_step(const KernelArgs&, const uint32_t*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_fill(uint32_t*, uint32_t, uint64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_base(const BaseArgs&, int, hipStream_t) { return hipSuccess; }
+}  // namespace lora
+
+// The runtime calls of the library's host code (defined here, they take the
+// place of the HIP library's).
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+    *v = a == hipDeviceAttributeNumberOfXccs ? 8 : 256;
+    return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t n) { return (*p = std::aligned_alloc(256, (n + 255) / 256 * 256)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) { *c = hipStreamCaptureStatusNone; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
+}
+
+namespace {
+
+int failures = 0;
+#define CHECK(cond, ...)                                   \
+    do {                                                   \
+        if (!(cond)) {                                     \
+            std::fprintf(stderr, "FAIL %s:%d: ", __FILE__, __LINE__); \
+            std::fprintf(stderr, __VA_ARGS__);             \
+            std::fprintf(stderr, "\n");                    \
+            ++failures;                                    \
+        }                                                  \
+    } while (0)
+
+alignas(16) unsigned char g_factor[16];    // stands for every factor: nothing reads it
+
+lora_table_t table(int h_in, int h_out, const std::vector<int32_t>& ranks) {
+    std::vector<const void*> p(ranks.size(), g_factor);
+    std::vector<float> s(ranks.size(), 1.f);
+    lora_table_t t = nullptr;
+    const int rc = lora_register_adapters(&t, 0, h_in, h_out, LORA_BF16, (int)ranks.size(), p.data(), p.data(),
+                                          ranks.data(), s.data(), nullptr);
+    CHECK(rc == LORA_OK, "register: %d %s", rc, lora_last_error());
+    return t;
+}
+
+// A plan made for a batch whose K ranges are cut by bytes holds a part of that
+// batch whose ranges are not, and says so beforehand.
+void check_parts_fit() {
+    const int wide = 7, narrow = 60;
+    std::vector<int32_t> ranks(wide, 128);
+    ranks.insert(ranks.end(), narrow, 16);
+    std::vector<int32_t> off(ranks.size() + 1), ad(ranks.size());
+    std::iota(off.begin(), off.end(), 0);
+    std::iota(ad.begin(), ad.end(), 0);
+    const lora_table_t t = table(8192, 264, ranks);
+    const lora_batch_t whole{wide + narrow, wide + narrow, off.data(), ad.data()};
+    lora_plan_t p = nullptr;
+    CHECK(lora_plan_create(&p, t, &whole, nullptr) == LORA_OK, "create: %s", lora_last_error());
+    size_t ws = 0, pb = 0;
+    CHECK(lora_workspace_bytes(t, &whole, &ws) == LORA_OK && lora_plan_bytes(t, &whole, &pb) == LORA_OK, "sizes");
+    for (int n : {1, 3, wide, 30, wide + narrow}) {
+        const lora_batch_t part{n, n, off.data(), ad.data()};
+        size_t ws1 = 0, pb1 = 0;
+        CHECK(lora_workspace_bytes(t, &part, &ws1) == LORA_OK && lora_plan_bytes(t, &part, &pb1) == LORA_OK, "sizes");
+        CHECK(ws1 <= ws && pb1 <= pb, "%d of %d tokens: %zu of %zu, %zu of %zu bytes", n, wide + narrow, ws1, ws, pb1, pb);
+        const int rc = lora_plan_update(p, nullptr, &part, nullptr);
+        CHECK(rc == LORA_OK, "update to %d tokens: %d %s", n, rc, lora_last_error());
+    }
+    lora_plan_destroy(p);
+    lora_release_adapters(t);
+}
+
+}  // namespace
+
+int main() {
+    check_parts_fit();
+    if (failures) {
+        std::fprintf(stderr, "%d checks failed\n", failures);
+        return 1;
+    }
+    std::printf("plan_calls: all checks passed\n");
+    return 0;
+}
