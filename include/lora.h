@@ -107,7 +107,10 @@ int lora_register_adapters(lora_table_t* out, int device, int h_in, int h_out, i
                            const int32_t* ranks, const float* scales, void* stream);
 
 /* Free the table's device copy. The caller's A/B memory is not touched.
- * The caller must make sure no enqueued call still uses the table. */
+ * The caller must make sure no enqueued call still uses the table.  Launches
+ * recorded in a graph read the device copy at every replay when the batch has
+ * more than 128 distinct adapters, in lora_plan_apply_multi and in
+ * lora_base_plan_apply: keep the table while such a graph may be replayed. */
 int lora_release_adapters(lora_table_t t);
 
 /* Bytes of device workspace that lora_shrink / lora_expand / lora_apply_fused
@@ -240,7 +243,9 @@ int lora_apply_fused_static(lora_table_t t, const lora_batch_t* b, const void* x
  * lora_plan_expand, whatever the timing.  Any table with the same h_in, h_out and
  * dtype whose adapters referenced by the batch have the same ranks may be
  * used (e.g. the same adapters' factors in another layer); the weight
- * pointers and scales travel in the launch arguments.  A mismatch returns
+ * pointers and scales travel with the launch (a recorded one of up to 128 distinct
+ * adapters holds them in its arguments; others may read them from the table's
+ * device copy when they run).  A mismatch returns
  * LORA_E_SHAPE / LORA_E_RANK / LORA_E_INDEX and enqueues nothing.
  *
  * lora_plan_shrink and lora_plan_expand are the two halves as separate

@@ -31,8 +31,10 @@
 //
 // A plan depends on the batch, the ranks and the shapes only.  The weight
 // pointers and scales of the groups it references travel in the kernel
-// arguments of each launch, so one plan serves every layer's adapter table of
-// the same ranks (the batch of a step is the same for all of them).
+// arguments of each launch (those past kKargGroups groups, of several projections
+// and of eager streamed steps are read from the device copies of the tables that
+// the arguments name), so one plan serves every layer's adapter table of the same ranks (the batch of a
+// step is the same for all of them).
 //
 // Both contractions run on MFMA (v_mfma_f32_16x16x32).  Shrink: v^T = A^T x^T,
 // K = h_in; A is transposed in registers (8 K rows x 8 ranks per lane) and
@@ -111,7 +113,7 @@ struct DevItem {
     int64_t part;        // float offset into the partial buffer
     int32_t kind;
     int32_t group;       // group of the batch (index into the launch's pointer table)
-    int32_t adapter;     // adapter index (registry fallback when group >= kKargGroups)
+    int32_t adapter;     // adapter index (the registry's entry: groups past kKargGroups, several projections)
     int32_t rank;
     int32_t nrows;       // rows in this item (<= 64)
     int32_t lo;

@@ -1303,7 +1303,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 lora_step_kernel(const DevItem* __restrict__ items, const uint32_t* __restrict__ hdr, KernelArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[kStepLds];
     Item it;
-    if constexpr (kLookup == kLookupArgs) {
+    // (streamed steps, of a round of items and more, pick their one entry by a scalar
+    // load: measured against the lane table, 70B-shaped q 86.4 and 90.1 us)
+    if constexpr (kLookup == kLookupArgs && !kStream) {
         const LaneTable lt = load_lane_table();       // in flight with the item and the header
         it = load_item(items + blockIdx.x);
         if (stale(hdr, a)) return;
@@ -1339,6 +1341,18 @@ hipError_t launch_expand(const KernelArgs& a, const uint32_t* hdr, int dtype, hi
     return hipGetLastError();
 }
 
+// Streamed steps read pointers and scales from the registry, whose lines stay in
+// the L2s, where they would find those of their arguments cold (65 adapters of rank 16
+// at 5120 -> 2768 14.0 against 14.5 us, 13B-shaped down 19.5 against 21.6, 70B-shaped
+// q 84.9 against 86.4).  A recorded one reads its arguments all the same: it may be
+// replayed when the table, whose memory the registry is, has been released.
+static bool recording(hipStream_t s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();                  // not known: arguments serve both
+    return true;
+}
+
 hipError_t launch_step(const KernelArgs& a, const uint32_t* hdr, int dtype, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.n_items), dim3(kThreads), 0, s, a.items, hdr, a); };
@@ -1347,12 +1361,12 @@ hipError_t launch_step(const KernelArgs& a, const uint32_t* hdr, int dtype, hipS
         if (a.n_proj > 1) {
             if (a.streams) go(lora_step_kernel<Fmt, kLookupMulti, true>);
             else go(lora_step_kernel<Fmt, kLookupMulti, false>);
-        } else if (a.streams) {               // large steps: the registry, for any number of groups
-            go(lora_step_kernel<Fmt, kLookupReg, true>);
-        } else if (a.n_groups <= kKargGroups) {
-            go(lora_step_kernel<Fmt, kLookupArgs, false>);
+        } else if (a.streams) {
+            if (a.n_groups > kKargGroups || !recording(s)) go(lora_step_kernel<Fmt, kLookupReg, true>);
+            else go(lora_step_kernel<Fmt, kLookupArgs, true>);
         } else {
-            go(lora_step_kernel<Fmt, kLookupReg, false>);
+            if (a.n_groups <= kKargGroups) go(lora_step_kernel<Fmt, kLookupArgs, false>);
+            else go(lora_step_kernel<Fmt, kLookupReg, false>);
         }
     };
     if (dtype == 0) pick(FmtF16{});

@@ -108,3 +108,28 @@ def test_long_contraction(dtype, ranks):
     assert np.array_equal(D.from_device_bits(y2), got)
     L.lora_plan_destroy(plan)
     dw.release()
+
+
+def test_recorded_launch_outlives_the_table():
+    """A recorded streamed step of up to 128 adapters carries their pointers and
+    scales, as every other step does: it replays after the table is released."""
+    print("recorded, table released", flush=True)
+    w = workload(W.BF16, 6152, [1])
+    dw = D.upload(w, DEV)
+    p, pr, x = dw.projections[0], w.projections[0], dw.xs["x"]
+    s = torch.cuda.current_stream(DEV)
+    plan = L.lora_plan_create(p.table, dw.batch, s)
+    y = p.y.clone()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        L.lora_plan_apply(plan, p.table, x, x.shape[1], y, p.h_out, torch.cuda.current_stream(DEV))
+    dw.release()
+    ref = oracle.lora_apply(w.seg_offset, w.seg_adapter, w.xs["x"], pr.A, pr.B, w.ranks, w.scales, pr.y, w.dtype)
+    for _ in range(3):
+        y.copy_(p.y)
+        g.replay()
+        L.lora_plan_status(plan, s)
+        compare(D.from_device_bits(y), ref, w.dtype, pr.name, mag=magnitude(w, pr.name))
+    del g
+    L.lora_plan_destroy(plan)
