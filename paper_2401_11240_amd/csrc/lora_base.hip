@@ -131,17 +131,26 @@ __device__ __forceinline__ void wait_vm() {
 // into LDS at lds + 16 * lane; lds is the same in every lane.  Inline assembly,
 // with no output: for the builtin the compiler waits for every such load in
 // flight before each LDS read.  wait_vm() and a barrier order the reads after
-// it.  (m0 is used by nothing else in these kernels.)
+// it.  The compiler looks for no hazards inside: the wait state after the write of m0
+// is here, those of the resource in rsrc_words().
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // m0 is reserved: nothing to preserve, the clobber is what is said
 __device__ __forceinline__ void lds_load16(const u32x4& r, uint32_t lds, int off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds), "v"(off), "s"(r) : "memory");
+                 :: "s"(lds), "v"(off), "s"(r) : "memory", "m0");
 }
-// The resource of make_rsrc() as four scalar words.
+#pragma clang diagnostic pop
+// The resource of make_rsrc() as four scalar words, five wait states (gfx9) after the
+// vector instructions that write them.  (In front of every load instead, the states cost
+// 1 to 2% of a launch.  No base kernel spills a scalar register, whose reload would be
+// another such write.)
 __device__ __forceinline__ u32x4 rsrc_words(const void* base, uint32_t bytes) {
     const uint64_t b = (uint64_t)base;
-    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b),
-                 (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) & 0xffffu,
-                 (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), (uint32_t)kRsrcWord3};
+    u32x4 r = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b),
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) & 0xffffu,
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), (uint32_t)kRsrcWord3};
+    asm volatile("s_nop 4" : "+s"(r));
+    return r;
 }
 
 // v_mfma_f32_32x32x16: A [32 x 16] lane l holds A[l % 32][8 (l / 32) .. +7];
