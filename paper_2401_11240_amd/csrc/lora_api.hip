@@ -42,7 +42,20 @@ __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a) {
     const uint32_t* data = (const uint32_t*)(args + offsetof(PlanArgs, data));
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
     const int t = threadIdx.x;
-    if ((int)blockIdx.x >= a.n_rows) {
+    const int n_item_blocks = a.n_rows * a.slices;
+    if ((int)blockIdx.x > n_item_blocks) {
+        // the partial and v blocks in both step buffers: the sentinel
+        u32x4* p0 = (u32x4*)(a.w + a.off_step_partials);
+        u32x4* p1 = p0 + a.pbuf / 4;
+        const u32x4 s4 = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+        const int64_t stride = (int64_t)(gridDim.x - n_item_blocks - 1) * kThreads;
+        for (int64_t q = (int64_t)(blockIdx.x - n_item_blocks - 1) * kThreads + t; q < a.arm_quads; q += stride) {
+            p0[q] = s4;
+            p1[q] = s4;
+        }
+        return;
+    }
+    if ((int)blockIdx.x == n_item_blocks) {
         if (a.first) {
             if (t < kHeaderBytes / 4) ((uint32_t*)a.w)[t] = t == 0 ? a.generation : 0u;
             const uint16_t* count = (const uint16_t*)(args + offsetof(PlanArgs, step_count));
@@ -53,15 +66,16 @@ __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a) {
         for (int q = t; q < a.blob_words; q += kThreads) ((uint32_t*)(a.w + a.off_blob))[q] = data[a.blob_at + q];
         return;
     }
-    const PlanRow r = ((const PlanRow*)data)[blockIdx.x];
+    const int slice = (int)blockIdx.x / a.n_rows, block = (int)blockIdx.x - slice * a.n_rows;
+    const PlanRow r = ((const PlanRow*)data)[block];
     const int32_t* rows = (const int32_t*)data + a.n_rows * kRowWords + (r.row0 >= 0 ? 0 : -1 - r.row0);
     const PlanDims d = *(const PlanDims*)(args + offsetof(PlanArgs, dims) + r.proj() * sizeof(PlanDims));
     const RowGeom g = row_geom(d, r.rank(), r.nrows());
-    const DevItem base = row_item(r, g, a.row_first + blockIdx.x, rows);
+    const DevItem base = row_item(r, g, a.row_first + block, rows);
     const int n_reduce = g.direct ? 0 : g.nslice;
     const int total = g.nsplit + n_reduce + g.ntiles + g.nslice;
     const int part = t & 7;                   // this thread's 16 bytes of an item
-    for (int q = t >> 3; q < total; q += kThreads / 8) {
+    for (int q = slice * (kThreads / 8) + (t >> 3); q < total; q += a.slices * (kThreads / 8)) {
         DevItem it = base;
         int c = q, at, queue = -1;            // place in its list, and in its XCD's queue
         uint64_t list;
@@ -99,19 +113,10 @@ __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a) {
         ((u32x4*)(a.w + list))[8 * (int64_t)at + part] = v;
         if (a.step_len && queue >= 0) ((u32x4*)(a.w + a.off_step))[8 * ((int64_t)queue * a.n_xcd + r.home) + part] = v;
     }
+    if (slice) return;
     int32_t* perm = (int32_t*)(a.w + a.off_perm) + r.p0;
     if (r.proj() == 0 && t < r.nrows()) perm[t] = r.row0 >= 0 ? r.row0 + t : rows[t];
-    if (a.arm) {
-        if (t == 0) ((uint32_t*)(a.w + a.off_sync))[(int64_t)(a.row_first + blockIdx.x) * kSyncStride] = 0u;
-        // the row block's partial and v blocks in both step buffers: the sentinel
-        float* p0 = (float*)(a.w + a.off_step_partials) + r.part;
-        const int n4 = (g.nsplit + 1) * g.pstride / 4;
-        const u32x4 s4 = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-        for (int q = t; q < n4; q += kThreads) {
-            ((u32x4*)p0)[q] = s4;
-            ((u32x4*)(p0 + a.pbuf))[q] = s4;
-        }
-    }
+    if (a.arm && t == 0) ((uint32_t*)(a.w + a.off_sync))[(int64_t)(a.row_first + block) * kSyncStride] = 0u;
 }
 
 }  // namespace lora
@@ -199,6 +204,7 @@ struct HostPlan {
     int n_shrink = 0, n_reduce = 0, n_expand = 0, n_all = 0;   // items of each list (n_all: lora_shrink's reduce items)
     int n_xcd = 1, step_len = 0;        // step grid laid out per XCD: slots per XCD (0: the lists' own order)
     uint16_t step_count[64];            // items in each XCD's queue
+    int max_items = 0;                  // items of a row block (in its lists together), at most
     int n_rows = 0;
     int64_t n_partials = 0;
     // The same of the plan without ranges cut by bytes: what it is sized for.
@@ -285,6 +291,7 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
     p.n_proj = 1;
     p.n_partials = 0;
     p.uncut = {};
+    p.max_items = 0;
     p.n_shrink = p.n_reduce = p.n_expand = p.n_all = 0;
 
     // Row blocks of more than 16 rows (prompt segments, popular adapters) are
@@ -386,6 +393,7 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
             p.n_reduce += q.direct ? 0 : q.nslice;
             p.n_expand += q.ntiles;
             p.n_all += q.nslice;
+            p.max_items = std::max(p.max_items, q.nsplit + (q.direct ? 1 : 2) * q.nslice + q.ntiles);
             // the row block's nsplit partial blocks, then its v block
             p.n_partials += (int64_t)(q.nsplit + 1) * q.pstride;
             p.rb_bytes.push_back((int64_t)(r + nb) * t->h_in * 2 + (int64_t)(r + 2 * nb) * t->h_out * 2);
@@ -421,6 +429,7 @@ int append_lists(HostPlan& p, const HostPlan& q, int c) {
     p.rb_bytes.insert(p.rb_bytes.end(), q.rb_bytes.begin(), q.rb_bytes.end());
     p.n_partials += q.n_partials;
     p.n_rb += q.n_rb;
+    p.max_items = std::max(p.max_items, q.max_items);
     p.uncut.shrink += q.uncut.shrink;
     p.uncut.reduce += q.uncut.reduce;
     p.uncut.all += q.uncut.all;
@@ -648,6 +657,7 @@ int write_plan(const HostPlan& p, unsigned char* w, bool arm, hipStream_t s, con
     a.arm = arm;
     a.n_xcd = p.n_xcd;
     a.step_len = p.step_len;
+    a.slices = std::max(1, std::min(kMaxSlices, (p.max_items + kSliceItems - 1) / kSliceItems));
     for (int c = 0; c < p.n_proj; ++c) a.dims[c] = p.dims[c];
     if (p.step_len) std::memcpy(a.step_count, p.step_count, sizeof(uint16_t) * p.n_xcd);
     size_t i = 0, blob_at = 0;
@@ -686,8 +696,10 @@ int write_plan(const HostPlan& p, unsigned char* w, bool arm, hipStream_t s, con
             a.off_blob = off_blob + 4 * blob_at;
             blob_at += m;
         }
+        a.arm_quads = first && arm ? (int32_t)(p.n_partials / 4) : 0;
+        const int arm_blocks = std::min(kArmBlocks, (a.arm_quads + kArmQuads - 1) / kArmQuads);
         first = false;
-        hipLaunchKernelGGL(lora_plan_kernel, dim3((unsigned)n + 1), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(lora_plan_kernel, dim3((unsigned)((int)n * a.slices + 1 + arm_blocks)), dim3(kThreads), 0, s, a);
         LORA_HIP_TRY(hipGetLastError());
     }
     return LORA_OK;

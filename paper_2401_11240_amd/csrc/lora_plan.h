@@ -3,7 +3,8 @@
 //
 // A call hands the device its row blocks (56 bytes each, and the rows of those
 // that are not consecutive) in the kernel arguments of lora_plan_kernel, which
-// expands them into the items (128 bytes each, 8 to 60 of them per block).
+// expands them into the items (128 bytes each; a few to some tens per block, over a
+// thousand at h_in and h_out in the tens of thousands).
 // Built on the host and copied from a pinned ring, the list bounded the one-shot
 // calls: a shrink and an expand call on 1491 rows (40 blocks, 1200 items) took
 // 86 us together against 39 us now, lora_apply_fused on 203 rows 39 against 20 us,
@@ -145,9 +146,11 @@ struct PlanArgs {
     uint64_t off_blob;           // where the launch's extra words go
     int64_t pbuf;                // floats from the first step buffer to the second
     uint32_t generation;
-    int32_t arm;                 // 1: also clear the counters and arm the step buffers (plans)
+    int32_t arm;                 // 1: also clear the counters (plans)
+    int32_t arm_quads;           // 16-byte values of a step buffer to arm in this launch (both buffers; 0: none)
     int32_t first;               // 1: the launch that writes the header and the empty slots of the step grid
     int32_t n_rows, row_first;   // row blocks in this launch, number of the first
+    int32_t slices;              // workgroups that share a row block's items
     int32_t n_xcd, step_len;     // step grid laid out per XCD: slots per XCD (0: none)
     int32_t blob_at, blob_words; // extra words in data
     PlanDims dims[kMaxProj];
@@ -157,8 +160,16 @@ struct PlanArgs {
 constexpr int kPlanWords = 912;
 static_assert(sizeof(PlanArgs) <= 4096, "kernel arguments");
 
-// One workgroup per row block: eight lanes write an item (16 bytes each).  A few
-// KB of arguments in, some hundred KB out: bounded by the launch (about 3 us).
+// Eight lanes write an item (16 bytes each), `slices` workgroups the items of a row
+// block, kSliceItems each; one workgroup writes the header, the empty slots and the extra
+// words, and the step buffers are armed by workgroups of their own, kArmQuads values
+// of each buffer apiece, up to kArmBlocks of them.  A few KB of arguments in, some
+// hundred KB of items out: about 3 us, the launch, where the step buffers are small.
+// Armed by the workgroup of the row block, a single compute unit wrote all of a large
+// block (29 MB at rank 256, h_in 28672): an update of 32 such rows
+// took 214 us against 7.5, one of 64 rows of rank 128 at 8192 35 against 5.4.
+constexpr int kSliceItems = 64, kMaxSlices = 16;
+constexpr int kArmQuads = 1024, kArmBlocks = 1024;
 __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a);
 
 }  // namespace lora

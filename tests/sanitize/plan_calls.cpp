@@ -36,10 +36,16 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) { *c = hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
+// a <<<>>> launch: its configuration pushed, popped by the kernel's stub, then the launch
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t);
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* s);
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void**, size_t, hipStream_t);
 }
 
 namespace {
+
+int g_launches, g_workgroups;              // of the kernel that writes the work list
+dim3 g_grid, g_block;
 
 int failures = 0;
 #define CHECK(cond, ...)                                   \
@@ -51,6 +57,28 @@ int failures = 0;
             ++failures;                                    \
         }                                                  \
     } while (0)
+
+}  // namespace
+
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t) {
+    g_grid = grid;
+    g_block = block;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* s) {
+    *grid = g_grid;
+    *block = g_block;
+    *lds = 0;
+    *s = nullptr;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void**, size_t, hipStream_t) {
+    ++g_launches;
+    g_workgroups += (int)grid.x;
+    return hipSuccess;
+}
+
+namespace {
 
 alignas(16) unsigned char g_factor[16];    // stands for every factor: nothing reads it
 
@@ -91,9 +119,33 @@ void check_parts_fit() {
     lora_release_adapters(t);
 }
 
+// An update arms the step buffers with the whole device: no workgroup writes more
+// than 64 KiB of them while there are fewer than 1024.
+void check_arming_is_spread() {
+    for (int rows : {1, 16, 32, 64}) {
+        for (int rank : {8, 64, 128, 256}) {
+            const lora_table_t t = table(28672, 8192, {rank});
+            std::vector<int32_t> off = {0, rows}, ad = {0};
+            const lora_batch_t b{rows, 1, off.data(), ad.data()};
+            lora_plan_t p = nullptr;
+            CHECK(lora_plan_create(&p, t, &b, nullptr) == LORA_OK, "create: %s", lora_last_error());
+            size_t ws = 0, pb = 0;                 // a plan's bytes are a workspace's and the step buffers'
+            CHECK(lora_workspace_bytes(t, &b, &ws) == LORA_OK && lora_plan_bytes(t, &b, &pb) == LORA_OK, "sizes");
+            g_launches = g_workgroups = 0;
+            CHECK(lora_plan_update(p, nullptr, &b, nullptr) == LORA_OK, "update: %s", lora_last_error());
+            CHECK(g_launches == 1, "%d launches", g_launches);
+            CHECK(g_workgroups >= 1024 || (pb - ws) / g_workgroups <= 65536, "rank %d, %d rows: %zu bytes by %d workgroups",
+                  rank, rows, pb - ws, g_workgroups);
+            lora_plan_destroy(p);
+            lora_release_adapters(t);
+        }
+    }
+}
+
 }  // namespace
 
 int main() {
+    check_arming_is_spread();
     check_parts_fit();
     if (failures) {
         std::fprintf(stderr, "%d checks failed\n", failures);
