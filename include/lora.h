@@ -270,7 +270,8 @@ int lora_plan_create(lora_plan_t* out, lora_table_t t, const lora_batch_t* b, vo
  * row blocks: one launch for about 60 of them), and returns.  No device or host
  * allocation, no copy, no memset, no synchronisation.  A batch that needs more than the
  * capacity returns LORA_E_WORKSPACE and leaves the plan as it was; errors of
- * b are those of lora_plan_create.  Updates and the plan's launches must be
+ * b are those of lora_plan_create.  After LORA_E_HIP the plan runs nothing (its
+ * launches report LORA_E_STALE) until an update succeeds.  Updates and the plan's launches must be
  * ordered on one stream.  lora_plan_update also clears the plan's status.
  *
  * Graphs.  lora_plan_apply, _shrink and _expand may be recorded in a HIP graph:

@@ -56,8 +56,9 @@ __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a) {
         return;
     }
     if ((int)blockIdx.x == n_item_blocks) {
+        uint32_t word;
+        if (t < kHeaderBytes / 4 && header_word(a, t, word)) ((uint32_t*)a.w)[t] = word;
         if (a.first) {
-            if (t < kHeaderBytes / 4) ((uint32_t*)a.w)[t] = t == 0 ? a.generation : 0u;
             const uint16_t* count = (const uint16_t*)(args + offsetof(PlanArgs, step_count));
             u32x4* step = (u32x4*)(a.w + a.off_step);
             for (int q = t; q < 8 * a.step_len * a.n_xcd; q += kThreads)
@@ -696,6 +697,7 @@ int write_plan(const HostPlan& p, unsigned char* w, bool arm, hipStream_t s, con
             a.off_blob = off_blob + 4 * blob_at;
             blob_at += m;
         }
+        a.last = i == p.rows.size() && blob_at == blob_words;
         a.arm_quads = first && arm ? (int32_t)(p.n_partials / 4) : 0;
         const int arm_blocks = std::min(kArmBlocks, (a.arm_quads + kArmQuads - 1) / kArmQuads);
         first = false;

@@ -149,6 +149,7 @@ struct PlanArgs {
     int32_t arm;                 // 1: also clear the counters (plans)
     int32_t arm_quads;           // 16-byte values of a step buffer to arm in this launch (both buffers; 0: none)
     int32_t first;               // 1: the launch that writes the header and the empty slots of the step grid
+    int32_t last;                // 1: the launch that completes the list
     int32_t n_rows, row_first;   // row blocks in this launch, number of the first
     int32_t slices;              // workgroups that share a row block's items
     int32_t n_xcd, step_len;     // step grid laid out per XCD: slots per XCD (0: none)
@@ -159,6 +160,14 @@ struct PlanArgs {
 };
 constexpr int kPlanWords = 912;
 static_assert(sizeof(PlanArgs) <= 4096, "kernel arguments");
+
+// Header word i after this launch, when it writes it: the generation only once the
+// list is complete, 0 (no plan's) until then, so that nothing runs a list whose later
+// launches failed.
+LORA_HD inline bool header_word(const PlanArgs& a, int i, uint32_t& v) {
+    v = i == 0 && a.last ? a.generation : 0u;
+    return a.first || (a.last && i == 0);
+}
 
 // Eight lanes write an item (16 bytes each), `slices` workgroups the items of a row
 // block, kSliceItems each; one workgroup writes the header, the empty slots and the extra

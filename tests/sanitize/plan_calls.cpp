@@ -11,6 +11,7 @@
 
 #include "lora.h"
 #include "lora_internal.h"
+#include "lora_plan.h"
 
 namespace lora {
 hipError_t launch_shrink(const KernelArgs&, const uint32_t*, int, hipStream_t) { return hipSuccess; }
@@ -35,7 +36,7 @@ hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) { *c = hipStreamCaptureStatusNone; return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError();
 // a <<<>>> launch: its configuration pushed, popped by the kernel's stub, then the launch
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t);
 hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* s);
@@ -44,8 +45,12 @@ hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void**, size_t, hipStre
 
 namespace {
 
-int g_launches, g_workgroups;              // of the kernel that writes the work list
+// of the kernel that writes the work list: how many (the g_fail_at-th from now on
+// fails), their workgroups, the generation the list's header holds after them
+int g_launches, g_workgroups, g_fail_at;
+uint32_t g_generation;
 dim3 g_grid, g_block;
+hipError_t g_error = hipSuccess;
 
 int failures = 0;
 #define CHECK(cond, ...)                                   \
@@ -60,6 +65,11 @@ int failures = 0;
 
 }  // namespace
 
+hipError_t hipGetLastError() {
+    const hipError_t e = g_error;
+    g_error = hipSuccess;
+    return e;
+}
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t) {
     g_grid = grid;
     g_block = block;
@@ -72,8 +82,11 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
     *s = nullptr;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void** args, size_t, hipStream_t) {
     ++g_launches;
+    if (g_fail_at > 0 && --g_fail_at == 0) return g_error = hipErrorOutOfMemory;
+    uint32_t v = 0;
+    if (lora::header_word(*(const lora::PlanArgs*)args[0], 0, v)) g_generation = v;
     g_workgroups += (int)grid.x;
     return hipSuccess;
 }
@@ -142,9 +155,36 @@ void check_arming_is_spread() {
     }
 }
 
+// A list written by several launches is no plan's until the last of them: when one
+// fails, neither launches recorded for the batch before nor those of the new one run it.
+void check_failed_update() {
+    std::vector<int32_t> ranks(4, 16), off(1025), ad(1024);
+    std::iota(off.begin(), off.end(), 0);
+    for (int i = 0; i < 1024; ++i) ad[i] = i % 4;                // 16 row blocks of rows four apart
+    const lora_table_t t = table(256, 264, ranks);
+    const lora_batch_t b{1024, 1024, off.data(), ad.data()};
+    lora_plan_t p = nullptr;
+    CHECK(lora_plan_create(&p, t, &b, nullptr) == LORA_OK, "create: %s", lora_last_error());
+    const uint32_t made = g_generation;
+    g_launches = 0;
+    CHECK(lora_plan_update(p, nullptr, &b, nullptr) == LORA_OK, "update: %s", lora_last_error());
+    const int n = g_launches;
+    CHECK(n >= 2 && g_generation == made + 1, "%d launches, generation %u after %u", n, g_generation, made);
+    for (int at = 1; at <= n; ++at) {
+        const uint32_t before = g_generation;
+        g_fail_at = at;
+        CHECK(lora_plan_update(p, nullptr, &b, nullptr) == LORA_E_HIP, "launch %d fails", at);
+        CHECK(at == 1 ? g_generation == before : g_generation == 0, "launch %d failed: generation %u", at, g_generation);
+        CHECK(lora_plan_update(p, nullptr, &b, nullptr) == LORA_OK && g_generation == before + 2, "update after a failure");
+    }
+    lora_plan_destroy(p);
+    lora_release_adapters(t);
+}
+
 }  // namespace
 
 int main() {
+    check_failed_update();
     check_arming_is_spread();
     check_parts_fit();
     if (failures) {
