@@ -35,20 +35,27 @@ using namespace lora;
 
 namespace lora {
 
+template <bool kStaged>
 __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a) {
     // read through the argument segment: a lane-dependent index into the
     // parameter would copy it to private memory
     const unsigned char* args = (const unsigned char*)__builtin_amdgcn_kernarg_segment_ptr();
-    const uint32_t* data = (const uint32_t*)(args + offsetof(PlanArgs, data));
+    const uint32_t* data = kStaged ? a.staged : (const uint32_t*)(args + offsetof(PlanArgs, data));
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
     const int t = threadIdx.x;
     const int n_item_blocks = a.n_rows * a.slices;
+    if ((int)blockIdx.x > n_item_blocks + a.arm_blocks) {
+        const int at = ((int)blockIdx.x - n_item_blocks - a.arm_blocks - 1) * kBlobWords;
+        uint32_t* dst = (uint32_t*)(a.w + a.off_blob);
+        for (int q = at + t; q < min_i(at + kBlobWords, a.blob_words); q += kThreads) dst[q] = data[a.blob_at + q];
+        return;
+    }
     if ((int)blockIdx.x > n_item_blocks) {
         // the partial and v blocks in both step buffers: the sentinel
         u32x4* p0 = (u32x4*)(a.w + a.off_step_partials);
         u32x4* p1 = p0 + a.pbuf / 4;
         const u32x4 s4 = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-        const int64_t stride = (int64_t)(gridDim.x - n_item_blocks - 1) * kThreads;
+        const int64_t stride = (int64_t)a.arm_blocks * kThreads;
         for (int64_t q = (int64_t)(blockIdx.x - n_item_blocks - 1) * kThreads + t; q < a.arm_quads; q += stride) {
             p0[q] = s4;
             p1[q] = s4;
@@ -64,7 +71,6 @@ __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a) {
             for (int q = t; q < 8 * a.step_len * a.n_xcd; q += kThreads)
                 if ((q >> 3) / a.n_xcd >= (int)count[(q >> 3) % a.n_xcd]) step[q] = u32x4{0u, 0u, 0u, 0u};
         }
-        for (int q = t; q < a.blob_words; q += kThreads) ((uint32_t*)(a.w + a.off_blob))[q] = data[a.blob_at + q];
         return;
     }
     const int slice = (int)blockIdx.x / a.n_rows, block = (int)blockIdx.x - slice * a.n_rows;
@@ -636,12 +642,92 @@ int check_not_capturing(hipStream_t s, const char* what) {
     return LORA_OK;
 }
 
+// Pinned host memory for lists too large for kernel arguments: kStageSlots slots per
+// device, allocated with the device's first table and given back with its last.  A
+// launch behind the one that reads a slot writes the slot's use number back; a slot is
+// taken again once its last use has come back, and the host never waits for one (no
+// event either: asking for one would break a capture on another stream).
+struct StageRing {
+    std::mutex mu;
+    int tables = 0;
+    uint32_t* host = nullptr;                 // kStageSlots times kStagedWords, then the use numbers
+    uint32_t* dev = nullptr;                  // the same as the device addresses it
+    uint32_t uses[kStageSlots] = {};          // last use of each slot
+    unsigned next = 0;
+    static constexpr size_t kWords = (size_t)kStageSlots * (kStagedWords + kSyncStride);
+    static size_t use_at(int slot) { return (size_t)kStageSlots * kStagedWords + (size_t)slot * kSyncStride; }
+};
+constexpr int kMaxDevices = 64;
+StageRing g_stage[kMaxDevices];
+
+// (on the device, current; a device without pinned memory writes every list from arguments)
+void stage_retain(int device) {
+    if (device >= kMaxDevices) return;
+    StageRing& r = g_stage[device];
+    std::lock_guard<std::mutex> lk(r.mu);
+    if (r.tables++) return;
+    if (hipHostMalloc((void**)&r.host, sizeof(uint32_t) * StageRing::kWords, hipHostMallocMapped | hipHostMallocCoherent) !=
+        hipSuccess)
+        r.host = nullptr;
+    if (!r.host || hipHostGetDevicePointer((void**)&r.dev, r.host, 0) != hipSuccess) {
+        r.dev = nullptr;
+        (void)hipGetLastError();
+    }
+    for (int i = 0; i < kStageSlots; ++i) {
+        r.uses[i] = 0;
+        if (r.host) r.host[StageRing::use_at(i)] = 0;
+    }
+}
+void stage_release(int device) {
+    if (device >= kMaxDevices) return;
+    StageRing& r = g_stage[device];
+    std::lock_guard<std::mutex> lk(r.mu);
+    if (--r.tables) return;
+    if (r.host) (void)hipHostFree(r.host);
+    r.host = nullptr;
+    r.dev = nullptr;
+}
+// A free slot, or -1 (the ring's mutex held).
+int stage_take(StageRing& r) {
+    if (!r.dev) return -1;
+    const int i = (int)(r.next % kStageSlots);
+    if (__atomic_load_n(r.host + StageRing::use_at(i), __ATOMIC_ACQUIRE) != r.uses[i]) return -1;
+    ++r.next;
+    return i;
+}
+
+// Row blocks of p from the i-th on, then their listed rows, into the room words at dst:
+// as many as fit.  Moves i past them and returns the words.
+size_t pack_rows(const HostPlan& p, size_t& i, size_t room, uint32_t* dst) {
+    const size_t i0 = i;
+    size_t words = 0;
+    for (; i < p.rows.size(); ++i) {
+        const size_t need = kRowWords + p.rows[i].listed();
+        if (words + need > room) break;
+        words += need;
+    }
+    const size_t lists = (i - i0) * kRowWords;
+    size_t at = lists;
+    for (size_t j = i0; j < i; ++j) {
+        PlanRow r = p.rows[j];
+        if (const int n = r.listed()) {
+            r.row0 = -1 - (int32_t)(at - lists);
+            std::memcpy(dst + at, p.perm.data() + r.p0, sizeof(int32_t) * n);
+            at += n;
+        }
+        std::memcpy(dst + (j - i0) * kRowWords, &r, sizeof r);
+    }
+    return words;
+}
+
 // Write plan p's header, work list and grouped row order into the memory at w
 // (and, for a plan, clear its counters and arm its step buffers), and blob_bytes
-// (a multiple of 4) from blob to w + off_blob: as many launches as the row
-// blocks take at up to kPlanWords words each (one for about 60 row blocks).
-// No allocation, no copy engine, nothing that the host or a later call waits for.
-int write_plan(const HostPlan& p, unsigned char* w, bool arm, hipStream_t s, const void* blob = nullptr,
+// (a multiple of 4) from blob to w + off_blob.  The data ride in the arguments of up to
+// kArgLaunches launches (64 row blocks of consecutive rows each, 11 of 64 listed rows);
+// more of them, some thousand scattered rows or runs, in pinned memory that one launch
+// reads.  No allocation, no copy engine, nothing
+// that the host or a later call waits for.
+int write_plan(const HostPlan& p, unsigned char* w, bool arm, int device, hipStream_t s, const void* blob = nullptr,
                size_t blob_bytes = 0, size_t off_blob = 0) {
     PlanArgs a{};
     a.w = w;
@@ -661,49 +747,38 @@ int write_plan(const HostPlan& p, unsigned char* w, bool arm, hipStream_t s, con
     a.slices = std::max(1, std::min(kMaxSlices, (p.max_items + kSliceItems - 1) / kSliceItems));
     for (int c = 0; c < p.n_proj; ++c) a.dims[c] = p.dims[c];
     if (p.step_len) std::memcpy(a.step_count, p.step_count, sizeof(uint16_t) * p.n_xcd);
-    size_t i = 0, blob_at = 0;
     const size_t blob_words = blob_bytes / 4;
-    bool first = true;
-    while (first || i < p.rows.size() || blob_at < blob_words) {
-        const size_t i0 = i;
-        size_t words = 0;                     // of the row blocks and their row lists
-        for (; i < p.rows.size(); ++i) {
-            const size_t need = kRowWords + (p.rows[i].row0 < 0 ? p.rows[i].nrows() : 0);
-            if (words + need > kPlanWords) break;
-            words += need;
-        }
-        const size_t n = i - i0;
-        size_t list = n * kRowWords;
-        for (size_t j = 0; j < n; ++j) {
-            PlanRow r = p.rows[i0 + j];
-            if (r.row0 < 0) {
-                const int32_t* src = p.perm.data() + r.p0;
-                const int nb = r.nrows();
-                r.row0 = -1 - (int32_t)(list - n * kRowWords);
-                std::memcpy(a.data + list, src, sizeof(int32_t) * nb);
-                list += nb;
-            }
-            std::memcpy(a.data + j * kRowWords, &r, sizeof r);
-        }
-        a.n_rows = (int32_t)n;
-        a.row_first = (int32_t)i0;
-        a.first = first;
-        a.blob_words = 0;
-        if (i == p.rows.size() && blob_at < blob_words && words < kPlanWords) {
-            const size_t m = std::min<size_t>(kPlanWords - words, blob_words - blob_at);
-            std::memcpy(a.data + words, (const unsigned char*)blob + 4 * blob_at, 4 * m);
-            a.blob_at = (int32_t)words;
-            a.blob_words = (int32_t)m;
-            a.off_blob = off_blob + 4 * blob_at;
-            blob_at += m;
-        }
-        a.last = i == p.rows.size() && blob_at == blob_words;
-        a.arm_quads = first && arm ? (int32_t)(p.n_partials / 4) : 0;
-        const int arm_blocks = std::min(kArmBlocks, (a.arm_quads + kArmQuads - 1) / kArmQuads);
-        first = false;
-        hipLaunchKernelGGL(lora_plan_kernel, dim3((unsigned)((int)n * a.slices + 1 + arm_blocks)), dim3(kThreads), 0, s, a);
+    size_t left = blob_words;                 // words not yet on their way
+    for (const PlanRow& r : p.rows) left += kRowWords + r.listed();
+    size_t i = 0, blob_at = 0;
+    a.first = 1;
+    do {
+        StageRing* ring = left > (size_t)kArgLaunches * kPlanWords && device < kMaxDevices ? &g_stage[device] : nullptr;
+        std::unique_lock<std::mutex> lk;
+        if (ring) lk = std::unique_lock<std::mutex>(ring->mu);
+        const int slot = ring ? stage_take(*ring) : -1;
+        const size_t room = slot >= 0 ? kStagedWords : kPlanWords;
+        uint32_t* data = slot >= 0 ? ring->host + (size_t)slot * kStagedWords : a.data;
+        a.staged = slot >= 0 ? ring->dev + (size_t)slot * kStagedWords : nullptr;
+        a.row_first = (int32_t)i;
+        const size_t words = pack_rows(p, i, room, data);
+        a.n_rows = (int32_t)(i - a.row_first);
+        a.blob_words = i == p.rows.size() ? (int32_t)std::min(room - words, blob_words - blob_at) : 0;
+        a.blob_at = (int32_t)words;
+        a.off_blob = off_blob + 4 * blob_at;
+        if (a.blob_words) std::memcpy(data + words, (const unsigned char*)blob + 4 * blob_at, 4 * (size_t)a.blob_words);
+        blob_at += a.blob_words;
+        left -= words + a.blob_words;
+        a.last = left == 0;
+        a.arm_quads = a.first && arm ? (int32_t)(p.n_partials / 4) : 0;
+        a.arm_blocks = std::min(kArmBlocks, (a.arm_quads + kArmQuads - 1) / kArmQuads);
+        const dim3 grid(a.n_rows * a.slices + 1 + a.arm_blocks + (a.blob_words + kBlobWords - 1) / kBlobWords);
+        if (slot >= 0) hipLaunchKernelGGL(lora_plan_kernel<true>, grid, dim3(kThreads), 0, s, a);
+        else hipLaunchKernelGGL(lora_plan_kernel<false>, grid, dim3(kThreads), 0, s, a);
         LORA_HIP_TRY(hipGetLastError());
-    }
+        if (slot >= 0) LORA_HIP_TRY(launch_fill(ring->dev + StageRing::use_at(slot), ++ring->uses[slot], 1, s));
+        a.first = 0;
+    } while (left);
     return LORA_OK;
 }
 
@@ -713,7 +788,6 @@ int write_plan(const HostPlan& p, unsigned char* w, bool arm, hipStream_t s, con
 // would be a host-side stand-in, not device memory): the first call on each
 // device looks the device address up and keeps it.
 constexpr size_t kScratchBytes = size_t(16) << 20;
-constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 std::mutex g_scratch_mu;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};
@@ -924,7 +998,7 @@ void plan_free(lora_plan_s* pl) {
 int plan_upload(lora_plan_s* pl, hipStream_t s) {
     if (++pl->generation == 0) pl->generation = 1;
     pl->plan.generation = pl->generation;
-    return write_plan(pl->plan, pl->dmem, true, s);
+    return write_plan(pl->plan, pl->dmem, true, pl->device, s);
 }
 
 }  // namespace
@@ -1001,6 +1075,7 @@ int lora_register_adapters(lora_table_t* out, int device, int h_in, int h_out, i
             return fail(LORA_E_HIP, std::string("adapter table upload: ") + hipGetErrorString(e));
         }
     }
+    stage_retain(device);
     *out = t;
     return LORA_OK;
 }
@@ -1010,6 +1085,7 @@ int lora_release_adapters(lora_table_t t) {
     if (t->dev) {
         DeviceGuard dg(t->device);
         (void)hipFree(t->dev);
+        stage_release(t->device);
     }
     delete t;
     return LORA_OK;
@@ -1103,7 +1179,7 @@ int lora_shrink(lora_table_t t, const lora_batch_t* b, const void* x, int64_t ld
     hipStream_t s = (hipStream_t)stream;
     if (int rc = check_not_capturing(s, "lora_shrink")) return rc;
     unsigned char* w = (unsigned char*)ws;
-    if (int rc = write_plan(p, w, false, s)) return rc;
+    if (int rc = write_plan(p, w, false, t->device, s)) return rc;
     if (int rc = enqueue(t, p, w, x, ldx, nullptr, 0, s, true)) return rc;
     KernelArgs a = make_args(t, p, w, kSpinLimit);
     a.items = (const DevItem*)(w + p.off_reduce_all);
@@ -1127,7 +1203,7 @@ int lora_expand(lora_table_t t, const lora_batch_t* b, const float* v, int64_t l
     hipStream_t s = (hipStream_t)stream;
     if (int rc = check_not_capturing(s, "lora_expand")) return rc;
     unsigned char* w = (unsigned char*)ws;
-    if (int rc = write_plan(p, w, false, s)) return rc;
+    if (int rc = write_plan(p, w, false, t->device, s)) return rc;
     KernelArgs a = make_args(t, p, w, kSpinLimit);
     a.items = (const DevItem*)(w + p.off_expand);
     a.n_items = p.n_expand;
@@ -1154,7 +1230,7 @@ int lora_apply_fused(lora_table_t t, const lora_batch_t* b, const void* x, int64
     hipStream_t s = (hipStream_t)stream;
     if (int rc = check_not_capturing(s, "lora_apply_fused")) return rc;
     unsigned char* w = (unsigned char*)ws;
-    if (int rc = write_plan(p, w, false, s)) return rc;
+    if (int rc = write_plan(p, w, false, t->device, s)) return rc;
     return enqueue(t, p, w, x, ldx, y, ldy, s);
 }
 
@@ -1410,7 +1486,7 @@ int lora_base_apply(lora_table_t t, const lora_batch_t* b, const void* x, int64_
     hipStream_t s = (hipStream_t)stream;
     if (int rc = check_not_capturing(s, "lora_base_apply")) return rc;
     unsigned char* w = (unsigned char*)ws;
-    if (int rc = write_plan(L.p, w, false, s, L.pieces_blob.data(), L.pieces_blob.size(), L.off_pieces)) return rc;
+    if (int rc = write_plan(L.p, w, false, t->device, s, L.pieces_blob.data(), L.pieces_blob.size(), L.off_pieces)) return rc;
     return base_run(t, L, n_rows, w, x, ldx, wt, ldw, w_span, y, ldy, s);
 }
 
@@ -1439,7 +1515,7 @@ int lora_base_plan_create(lora_base_plan_t* out, lora_table_t t, const lora_batc
         return fail(LORA_E_NOMEM, std::string("hipMalloc of the base plan: ") + hipGetErrorString(e));
     }
     const BaseLayout& L = pl->L;
-    if (int rc = write_plan(L.p, pl->dmem, false, s, L.pieces_blob.data(), L.pieces_blob.size(), L.off_pieces)) {
+    if (int rc = write_plan(L.p, pl->dmem, false, t->device, s, L.pieces_blob.data(), L.pieces_blob.size(), L.off_pieces)) {
         (void)hipFree(pl->dmem);
         delete pl;
         return rc;
@@ -1496,7 +1572,7 @@ int lora_apply_fused_static(lora_table_t t, const lora_batch_t* b, const void* x
     if (int rc = check_not_capturing(s, "lora_apply_fused_static")) return rc;
     unsigned char* w = nullptr;
     if (int rc = scratch_address(t->device, &w)) return rc;
-    if (int rc = write_plan(p, w, false, s)) return rc;
+    if (int rc = write_plan(p, w, false, t->device, s)) return rc;
     return enqueue(t, p, w, x, ldx, y, ldy, s);
 }
 

@@ -29,7 +29,8 @@ struct PlanRow {
     int32_t group, adapter;
     int32_t shape;           // rank | rows << 16 | projection << 24
     int32_t p0;              // position of the first row in the grouped row order
-    int32_t row0;            // the first row when they are consecutive; else -1 - (their place in the row list)
+    int32_t row0;            // the first row when they are consecutive; else -1 - (their place in the row
+                             // list, where a projection past the first passes only inline rows)
     uint32_t part;           // float offset of its first partial block
     int32_t shrink_at, reduce_at, expand_at, all_at;   // its first item in each list
     int32_t home;            // XCD, and its first items in that XCD's queue (grid laid out per XCD)
@@ -37,6 +38,9 @@ struct PlanRow {
     LORA_HD int rank() const { return shape & 0xffff; }
     LORA_HD int nrows() const { return (shape >> 16) & 0xff; }
     LORA_HD int proj() const { return shape >> 24; }
+    // rows in the row list: not the consecutive ones, and once for all projections where
+    // only the grouped row order holds them
+    LORA_HD int listed() const { return row0 < 0 && (proj() == 0 || nrows() <= kInlineRows) ? nrows() : 0; }
 };
 static_assert(sizeof(PlanRow) == 56, "PlanRow layout");
 constexpr int kRowWords = sizeof(PlanRow) / 4;
@@ -154,11 +158,21 @@ struct PlanArgs {
     int32_t slices;              // workgroups that share a row block's items
     int32_t n_xcd, step_len;     // step grid laid out per XCD: slots per XCD (0: none)
     int32_t blob_at, blob_words; // extra words in data
+    int32_t arm_blocks;          // workgroups that arm
+    const uint32_t* staged;      // data in pinned host memory, instead of the one below
     PlanDims dims[kMaxProj];
     uint16_t step_count[64];     // items in each XCD's queue
-    uint32_t data[912];          // row blocks, then the rows of those not consecutive, then the extra words
+    uint32_t data[896];          // row blocks, then the rows of those not consecutive, then the extra words
 };
-constexpr int kPlanWords = 912;
+constexpr int kPlanWords = 896;
+// A list whose data take more than this many launches' arguments is written by one
+// launch that reads them from pinned host memory (256 KiB at a time), while one of the
+// device's slots is free.  lora_apply_fused at 1024 x 1024 with listed rows, a chain of
+// launches against pinned memory: 1 launch 25 and 31 us, 2 31 and 32, 3 40 and 35, 6 64
+// and 36, 12 95 and 44.
+constexpr int kArgLaunches = 2;
+constexpr int kStagedWords = 64 * 1024, kStageSlots = 8;
+constexpr int kBlobWords = 1024;   // extra words per workgroup
 static_assert(sizeof(PlanArgs) <= 4096, "kernel arguments");
 
 // Header word i after this launch, when it writes it: the generation only once the
@@ -170,8 +184,8 @@ LORA_HD inline bool header_word(const PlanArgs& a, int i, uint32_t& v) {
 }
 
 // Eight lanes write an item (16 bytes each), `slices` workgroups the items of a row
-// block, kSliceItems each; one workgroup writes the header, the empty slots and the extra
-// words, and the step buffers are armed by workgroups of their own, kArmQuads values
+// block, kSliceItems each; one workgroup writes the header and the empty slots, others the
+// extra words, kBlobWords each, and the step buffers are armed by workgroups of their own, kArmQuads values
 // of each buffer apiece, up to kArmBlocks of them.  A few KB of arguments in, some
 // hundred KB of items out: about 3 us, the launch, where the step buffers are small.
 // Armed by the workgroup of the row block, a single compute unit wrote all of a large
@@ -179,6 +193,7 @@ LORA_HD inline bool header_word(const PlanArgs& a, int i, uint32_t& v) {
 // took 214 us against 7.5, one of 64 rows of rank 128 at 8192 35 against 5.4.
 constexpr int kSliceItems = 64, kMaxSlices = 16;
 constexpr int kArmQuads = 1024, kArmBlocks = 1024;
+template <bool kStaged>
 __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a);
 
 }  // namespace lora

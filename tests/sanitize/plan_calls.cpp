@@ -1,6 +1,7 @@
 // The host side of the plan and one-shot calls against a stand-in HIP runtime:
 // device memory is host memory, launches are recorded and not run.  Built with
 // AddressSanitizer and UndefinedBehaviorSanitizer on the host code; no GPU.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -18,7 +19,7 @@ hipError_t launch_shrink(const KernelArgs&, const uint32_t*, int, hipStream_t) {
 hipError_t launch_expand(const KernelArgs&, const uint32_t*, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_reduce(const KernelArgs&, const uint32_t*, hipStream_t) { return hipSuccess; }
 hipError_t launch_step(const KernelArgs&, const uint32_t*, int, hipStream_t) { return hipSuccess; }
-hipError_t launch_fill(uint32_t*, uint32_t, uint64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_fill(uint32_t* p, uint32_t v, uint64_t n, hipStream_t);
 hipError_t launch_base(const BaseArgs&, int, hipStream_t) { return hipSuccess; }
 }  // namespace lora
 
@@ -33,6 +34,9 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
 }
 hipError_t hipMalloc(void** p, size_t n) { return (*p = std::aligned_alloc(256, (n + 255) / 256 * 256)) ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n); }
+hipError_t hipHostFree(void* p) { return hipFree(p); }
+hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) { *c = hipStreamCaptureStatusNone; return hipSuccess; }
@@ -48,6 +52,9 @@ namespace {
 // of the kernel that writes the work list: how many (the g_fail_at-th from now on
 // fails), their workgroups, the generation the list's header holds after them
 int g_launches, g_workgroups, g_fail_at;
+bool g_hold;
+std::vector<uint32_t> g_blob;              // the extra words of the launches, in order
+std::vector<int32_t> g_rows;               // the rows they list, in grouped order
 uint32_t g_generation;
 dim3 g_grid, g_block;
 hipError_t g_error = hipSuccess;
@@ -65,6 +72,11 @@ int failures = 0;
 
 }  // namespace
 
+// (g_hold: fills do not get through, as on a stream with earlier work)
+hipError_t lora::launch_fill(uint32_t* p, uint32_t v, uint64_t n, hipStream_t) {
+    if (!g_hold) std::fill(p, p + n, v);
+    return hipSuccess;
+}
 hipError_t hipGetLastError() {
     const hipError_t e = g_error;
     g_error = hipSuccess;
@@ -85,8 +97,17 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void** args, size_t, hipStream_t) {
     ++g_launches;
     if (g_fail_at > 0 && --g_fail_at == 0) return g_error = hipErrorOutOfMemory;
+    const lora::PlanArgs& a = *(const lora::PlanArgs*)args[0];
     uint32_t v = 0;
-    if (lora::header_word(*(const lora::PlanArgs*)args[0], 0, v)) g_generation = v;
+    if (lora::header_word(a, 0, v)) g_generation = v;
+    const uint32_t* data = a.staged ? a.staged : a.data;
+    g_blob.insert(g_blob.end(), data + a.blob_at, data + a.blob_at + a.blob_words);
+    for (int i = 0; i < a.n_rows; ++i) {
+        const lora::PlanRow& r = ((const lora::PlanRow*)data)[i];
+        const int32_t* listed = (const int32_t*)data + a.n_rows * lora::kRowWords + (-1 - r.row0);
+        if (r.proj() == 0)
+            for (int j = 0; j < r.nrows(); ++j) g_rows.push_back(r.row0 >= 0 ? r.row0 + j : listed[j]);
+    }
     g_workgroups += (int)grid.x;
     return hipSuccess;
 }
@@ -181,9 +202,73 @@ void check_failed_update() {
     lora_release_adapters(t);
 }
 
+// Lists of more data than a few launches' arguments hold are written by one launch
+// that reads pinned memory, as long as a slot of it is free, and by a chain of launches
+// when none is; the row order and the base projection's tile list come out the same.
+void check_staged_lists() {
+    const int n = 8192;
+    std::vector<int32_t> ranks(128, 16), off(n + 1), ad(n);
+    std::iota(off.begin(), off.end(), 0);
+    for (int i = 0; i < n; ++i) ad[i] = i % 128;
+    const lora_table_t t = table(256, 264, ranks);
+    const lora_table_t t2 = table(256, 520, ranks);
+    const lora_batch_t b{n, n, off.data(), ad.data()};
+    std::vector<int32_t> perm(n), goff(n + 1), gad(n);
+    int32_t G = 0;
+    CHECK(lora_group_rows(&b, 128, perm.data(), goff.data(), gad.data(), &G) == LORA_OK, "group");
+    lora_plan_t p = nullptr;
+    CHECK(lora_plan_create(&p, t, &b, nullptr) == LORA_OK, "create: %s", lora_last_error());
+    for (const bool hold : {false, true}) {
+        g_hold = hold;
+        for (int k = 0; k < 12; ++k) {                           // more than there are slots
+            g_launches = 0;
+            g_rows.clear();
+            CHECK(lora_plan_update(p, nullptr, &b, nullptr) == LORA_OK, "update: %s", lora_last_error());
+            CHECK(g_rows == perm, "row order");
+            CHECK(!hold || k < 8 ? g_launches == 1 : g_launches > 4, "held %d, call %d: %d launches", hold, k, g_launches);
+        }
+    }
+    lora_plan_destroy(p);
+    lora_release_adapters(t);
+    lora_release_adapters(t2);                                   // the ring goes, with what was held
+    g_hold = false;
+    const lora_table_t t3 = table(256, 264, ranks), t4 = table(256, 520, ranks);
+    // two projections list their scattered rows once: 16 blocks of 64 rows take two launches'
+    // arguments, and 14 words more per block of the second
+    const lora_table_t both[] = {t3, t4};
+    const lora_batch_t few{1024, 1024, off.data(), ad.data()};
+    for (int i = 0; i < 1024; ++i) ad[i] = i % 16;
+    for (int m : {1, 2}) {
+        g_launches = 0;
+        CHECK(lora_plan_create_multi(&p, m, both, &few, nullptr) == LORA_OK, "multi: %s", lora_last_error());
+        CHECK(g_launches == 2, "%d projections: %d launches", m, g_launches);
+        lora_plan_destroy(p);
+    }
+    // the base projection's tile list
+    for (int i = 0; i < n; ++i) ad[i] = i % 128;
+    lora_base_plan_t bp = nullptr;
+    g_blob.clear();
+    g_launches = 0;
+    CHECK(lora_base_plan_create(&bp, t3, &b, nullptr) == LORA_OK, "base: %s", lora_last_error());
+    CHECK(g_launches == 1, "%d launches", g_launches);
+    const std::vector<uint32_t> staged = g_blob;
+    lora_base_plan_destroy(bp);
+    g_hold = true;
+    for (int k = 0; k < 9; ++k) {
+        g_blob.clear();
+        CHECK(lora_base_plan_create(&bp, t3, &b, nullptr) == LORA_OK, "base: %s", lora_last_error());
+        CHECK(g_blob == staged && staged.size() >= 4 * (size_t)n, "tile list, call %d: %zu words", k, g_blob.size());
+        lora_base_plan_destroy(bp);
+    }
+    g_hold = false;
+    lora_release_adapters(t3);
+    lora_release_adapters(t4);
+}
+
 }  // namespace
 
 int main() {
+    check_staged_lists();
     check_failed_update();
     check_arming_is_spread();
     check_parts_fit();

@@ -1,10 +1,10 @@
 """The kernel that writes a work list into device memory, at the edges of what
-one launch of it carries (912 words: 65 row blocks of consecutive rows, fewer
+one launch of it carries (896 words: 64 row blocks of consecutive rows, fewer
 when their rows are listed): batches of 64, 65, 66 and 131 row blocks, blocks of
-1 to 64 scattered rows, a batch of one row and a plan updated from one to the
-other, through the one-shot call, the plan and the base projection (whose tile
-list rides in the same launches).  Every row against the oracle; the two delta
-forms bit for bit.
+1 to 64 scattered rows, so many of them that the list is read from pinned memory,
+a batch of one row and a plan updated from one to the other, through the one-shot
+call, the plan and the base projection (whose tile list rides in the same
+launches).  Every row against the oracle; the two delta forms bit for bit.
 """
 import numpy as np
 import pytest
@@ -41,6 +41,7 @@ CASES = {
     "scattered16": interleaved(40, 16) + (40,),
     "scattered64": interleaved(15, 64) + (15,),
     "scattered70": interleaved(14, 70) + (14,),
+    "scattered5000": interleaved(10, 500) + (10,),
     "mixed": ([1, 200, 1, 1, 64, 1, 65, 3], [0, 1, 2, 0, 3, -1, 1, 0], 4),
 }
 
@@ -96,11 +97,38 @@ def test_written_lists(name):
     do.release()
 
 
-@pytest.mark.parametrize("name", ["one", "65", "scattered64", "mixed"])
+@pytest.mark.parametrize("name", ["one", "65", "scattered64", "scattered5000", "mixed"])
 def test_written_base_tiles(name):
     print("base tiles", name, flush=True)
     w = workload(name, base=True)
     dw = D.upload(w, DEV)
     rows = np.arange(w.n_rows)
     compare(run_base(dw, w), oracle_rows(w, rows), w.dtype, name, mag=allowance(w, rows))
+    dw.release()
+
+
+def test_pinned_slots_in_turn():
+    """Lists read from pinned memory, call after call with no wait between, past the
+    number of slots: two batches in turn, each call with its own rows."""
+    print("pinned slots", flush=True)
+    lens, sa, n_ad = CASES["scattered5000"]
+    w = workload("scattered5000")
+    dw = D.upload(w, DEV)
+    p, x = dw.projection("proj"), dw.xs["x"]
+    s = torch.cuda.current_stream(DEV)
+    batches = [dw.batch, L.Batch(w.seg_offset, [(7 * a + 3) % n_ad for a in sa])]
+    room = max(L.lora_workspace_bytes(p.table, b) for b in batches)
+    ws = torch.empty(room, dtype=torch.uint8, device=DEV)
+    ys = [p.y.clone() for _ in range(24)]
+    for i, y in enumerate(ys):
+        L.lora_apply_fused(p.table, batches[i % 2], x, x.shape[1], y, y.shape[1], ws, room, s)
+    torch.cuda.synchronize()
+    pr = w.projections[0]
+    for k in (0, 1):
+        ref = oracle.lora_apply(w.seg_offset, np.asarray(batches[k].seg_adapter), w.xs["x"], pr.A, pr.B, w.ranks, w.scales,
+                                pr.y, w.dtype)
+        got = D.from_device_bits(ys[k])
+        compare(got, ref, w.dtype, f"batch {k}")
+        for y in ys[k::2]:
+            assert np.array_equal(D.from_device_bits(y), got)
     dw.release()
