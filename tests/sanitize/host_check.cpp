@@ -5,6 +5,7 @@
 //   * lora_group_rows equals the oracle's grouping, array for array;
 //   * lora_plan_inspect lists a work list whose shrink K ranges, expand
 //     column tiles and reduce slices cover each row block exactly once;
+//   * every shrink item's passes fit the LDS of the body that runs it;
 //   * malformed batches are refused with the documented codes;
 //   * the oracle's apply equals its shrink followed by its expand, and its
 //     one-row form equals the matching row of the full result.
@@ -21,6 +22,7 @@
 
 #include "lora.h"
 #include "lora_internal.h"
+#include "lora_plan.h"
 #include "lora_sched.h"
 #include "lora_coldstart.h"
 
@@ -189,6 +191,48 @@ void check_long_plans() {
                 for (const auto& q : it)
                     if (q.kind == 1) CHECK(k[q.row_block] == h_in, "h_in %d rank %d rows %d: K %lld", h_in, rank, rows, (long long)k[q.row_block]);
             }
+}
+
+// Every way a K range can be cut: a shrink item's passes fit the LDS of the body that
+// runs it (the ring's buffers, or the register-staged body's space), its waves' sums the
+// LDS they are added in, and every range its body.
+void check_shrink_bodies() {
+    using namespace lora;
+    int streamed = 0;
+    for (int rep = 0; rep < 200000; ++rep) {
+        const int rank = rep % 2 ? 8 * rint_in(1, 32) : rint_in(1, 256);
+        const int nrows = rint_in(1, row_block(rank));
+        PlanDims d{};
+        d.h_in = 8 * rint_in(1, 4000);
+        d.h_out = 64;
+        d.big_split = rint_in(1, 512);
+        if (rnd() % 2) {
+            d.items = rint_in(512, 2000);
+            d.units = rint_in(nrows + rank, 20000);
+        }
+        const RowGeom g = row_geom(d, rank, nrows);
+        const int c = rint_in(0, g.nsplit - 1);
+        DevItem it{};
+        it.rank = rank;
+        it.nrows = nrows;
+        to_shrink(it, d, g, c);
+        const bool ring = shrink_uses_dma(rank, nrows) || (it.sub & kSubDma);
+        const int sub = it.sub & (kSubDma - 1), ms = msub_body(nrows), rp = round_up_i(rank, 16);
+        CHECK(sub >= 32 && sub % 32 == 0, "sub %d", sub);
+        if (it.sub & kSubDma) {
+            ++streamed;
+            CHECK(ms == 1 && d.items > 0 && it.len > g.sub, "a streamed item of %d rows, %d K", nrows, it.len);
+        }
+        if (ring) {
+            CHECK(rank % 8 == 0 && round_up_i(sub * (rank / 8), 64) + 2 * ms * sub <= kStageChunks, "rank %d sub %d rows %d", rank, sub, nrows);
+            const int wk = 4 / shrink_wn_split(rank);
+            CHECK(wk == 1 || wk * ms * 16 * (rp + 4) * 4 <= kShrinkLds, "rank %d rows %d: sums", rank, nrows);
+            CHECK(shrink_tq_of(rank, shrink_wn_split(rank)) * shrink_wn_split(rank) * 16 >= rp, "rank %d: tiles", rank);
+        } else {
+            CHECK(sub == g.sub && shrink_lds_bytes(rank, sub, nrows) <= kShrinkLds, "rank %d sub %d rows %d", rank, sub, nrows);
+        }
+    }
+    CHECK(streamed > 1000, "%d streamed items", streamed);
 }
 
 void check_errors(int n_adapters) {
@@ -370,6 +414,7 @@ int main() {
         check_plan(b, n_adapters);
     }
     check_long_plans();
+    check_shrink_bodies();
     check_errors(7);
     check_oracle();
     check_sched(200);

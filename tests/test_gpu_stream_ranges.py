@@ -2,7 +2,7 @@
 with at least a round of one-pass items): blocks of 1 to 16 rows, ranks with one
 to fifteen 16-rank tiles (waves splitting K four, two and one ways), ranks that
 are not a multiple of 8 and one too wide to stream beside them, h_in that no
-pass divides.  Every row against the oracle; the step launch, the separate
+pass divides, prompt blocks cut by bytes in the same step.  Every row against the oracle; the step launch, the separate
 launches and a launch of two projections bit for bit.
 """
 import numpy as np
@@ -28,7 +28,7 @@ DEV = torch.device("cuda:0")
 RANKS = [24, 64, 128, 16, 40, 240, 32, 12, 8, 256, 96, 48]
 
 
-def workload(dtype, h_in, rows):
+def workload(dtype, h_in, rows, prompts=()):
     n = 4 * len(RANKS)
     lens, sa = [], []
     for g in range(n):
@@ -36,18 +36,28 @@ def workload(dtype, h_in, rows):
             lens.append(1)
             sa.append(g)
     order = np.random.default_rng(3).permutation(len(sa))
+    sa = [sa[i] for i in order] + [3 * i % n for i in range(len(prompts))]
+    lens += prompts
     return W.build_workload(name="stream", seed=31, dtype=dtype, n_adapters=n, fixed_ranks=RANKS * 4,
-                            seg_adapter=[sa[i] for i in order], seg_lens=lens,
+                            seg_adapter=sa, seg_lens=lens,
                             projections=(("a", h_in, 264, "x"), ("b", h_in, 520, "x")))
 
 
-@pytest.mark.parametrize("dtype,h_in,rows", [(W.F16, 8200, [1]), (W.BF16, 6152, [1, 3, 16, 2]), (W.BF16, 8192, [16])])
-def test_streamed_ranges(dtype, h_in, rows):
-    print("stream", dtype, h_in, rows, flush=True)
-    w = workload(dtype, h_in, rows)
+# prompt segments beside: blocks of two and four 16-row subtiles, ranks that stream and that do not
+PROMPTS = [17, 64, 33, 130, 40]
+
+
+@pytest.mark.parametrize("dtype,h_in,rows,prompts", [(W.F16, 8200, [1], []), (W.BF16, 6152, [1, 3, 16, 2], []),
+                                                     (W.BF16, 8192, [16], []), (W.F16, 6152, [1], PROMPTS),
+                                                     (W.BF16, 8200, [1, 2], PROMPTS)])
+def test_streamed_ranges(dtype, h_in, rows, prompts):
+    print("stream", dtype, h_in, rows, prompts, flush=True)
+    w = workload(dtype, h_in, rows, prompts)
     items = L.lora_plan_inspect(L.Batch(w.seg_offset, w.seg_adapter), h_in, 264, w.ranks, 8)
     sh = items[(items["kind"] == 1) & (items["nrows"] <= 16)]
     assert (sh["len"] > sh["sub"]).any()       # the batch takes the streamed path
+    if prompts:                                # its larger blocks cut by bytes too: not all into as many ranges
+        assert np.unique(items["nsplit"][(items["kind"] == 1) & (items["nrows"] > 16)]).size > 1
     dw = D.upload(w, DEV)
     s = torch.cuda.current_stream(DEV)
     x = dw.xs["x"]

@@ -51,10 +51,16 @@ def check_lds_fit(rank, nrows, sh, ex):
     pass of a block of more than 16 rows (rank a multiple of 8) in one
     16 KiB buffer of the LDS-staged body (A rows rounded to whole 1 KiB wave
     loads, then the x rows), other passes in the register-staged body's
-    space; an expand item's v fragments below the y tile, its y tile (and
+    space; a decode block whose range has several passes streams through the
+    buffers too; an expand item's v fragments below the y tile, its y tile (and
     the columns it walks) within the rest."""
     ms = 1 if nrows <= 16 else (2 if nrows <= 32 else 4)
     rp = ceil_to(rank, 16)
+    if ms == 1 and rank % 8 == 0 and len(sh) < 2048:       # (4096 ranges at most: there registers take several passes)
+        for it in sh[sh["len"] > sh["sub"]]:
+            sub = int(it["sub"])
+            assert ceil_to(sub * (rank // 8), 64) + 2 * sub <= STAGE_CHUNKS, (rank, nrows, sub)
+            assert sub % 64 == 0 or sub == 32
     for sub in set(sh["sub"].tolist()):
         stage = ceil_to(sub * (rank // 8), 64) + 2 * ms * sub
         if ms > 1 and rank % 8 == 0 and stage <= STAGE_CHUNKS:
@@ -162,6 +168,56 @@ def test_long_contractions(h_in, ranks):
     items = L.lora_plan_inspect(b, h_in, 264, ranks, n_xcd=8)
     check_plan(items, h_in, 264, 8)
     assert items["nsplit"].max() <= 4096
+
+
+def streamed_blocks(items):
+    """Decode row blocks with K ranges of several passes."""
+    sh = items[(items["kind"] == KIND_SHRINK) & (items["nrows"] <= 16) & (items["len"] > items["sub"])]
+    return np.unique(sh["row_block"])
+
+
+STREAMED = {
+    "65 of rank 16": (5120, 2768, [16] * 65, [1] * 65, list(range(65))),
+    "70B-shaped": (8192, 28672, [8, 16, 32, 64, 128] * 25, [1] * 256 + [512] * 4, None),
+    "13B-shaped down": (13824, 5120, [8, 16, 32, 64] * 16, [1] * 128, None),
+    "odd ranks beside": (8200, 264, [24, 64, 128, 12, 40, 240, 32, 4, 8, 256, 96, 48] * 6, [1] * 144, None),
+    "prompts beside": (6152, 520, [16, 64, 128, 32] * 20, [1] * 100 + [17, 64, 130, 33], None),
+}
+
+
+@pytest.mark.parametrize("name", list(STREAMED))
+def test_streamed_plans(name):
+    """Batches over the line from which K ranges are cut by bytes: the same
+    properties, the decode blocks streaming, and no row block in more ranges than
+    one-pass items (prompt blocks: their share of about one round) would make."""
+    h_in, h_out, ranks, lens, sa = STREAMED[name]
+    if sa is None:
+        sa = np.random.default_rng(len(lens)).integers(0, len(ranks), size=len(lens)).tolist()
+    b = L.Batch(np.concatenate([[0], np.cumsum(lens)]), sa)
+    items = L.lora_plan_inspect(b, h_in, h_out, ranks, n_xcd=8)
+    check_plan(items, h_in, h_out, 8)
+    assert len(streamed_blocks(items)) > 10
+    shrink = items[items["kind"] == KIND_SHRINK]
+    _, first = np.unique(shrink["row_block"], return_index=True)
+    big = int((shrink["nrows"][first] > 16).sum())
+    for it in shrink[first]:
+        rank, nrows = int(it["rank"]), int(it["nrows"])
+        if nrows > 16:
+            assert it["nsplit"] <= -(-512 // big)
+        elif rank % 8 == 0:                    # one pass: at most 512 K of at most 32 KiB of A
+            assert it["nsplit"] <= -(-h_in // min(512, 64 * (256 // rank), 16384 // rank // 32 * 32))
+
+
+@pytest.mark.parametrize("seed", range(20))
+def test_random_large_decode_plans(seed):
+    rng = np.random.default_rng(7000 + seed)
+    n = int(rng.integers(30, 180))
+    ranks = rng.choice([16, 24, 32, 64, 128, 200, 12], size=n, p=[.3, .1, .2, .2, .1, .05, .05]).tolist()
+    lens = [1] * int(rng.integers(n, 280)) + [int(v) for v in rng.integers(17, 300, size=int(rng.integers(0, 4)))]
+    h_in, h_out = 8 * int(rng.integers(512, 3600)), 8 * int(rng.integers(33, 500))
+    b = L.Batch(np.concatenate([[0], np.cumsum(lens)]), rng.integers(0, n, size=len(lens)).tolist())
+    for n_xcd in (1, 8):
+        check_plan(L.lora_plan_inspect(b, h_in, h_out, ranks, n_xcd=n_xcd), h_in, h_out, n_xcd)
 
 
 def test_decode_headline_is_laid_out_and_few_adapters_are_not():
