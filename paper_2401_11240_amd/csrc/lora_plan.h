@@ -71,7 +71,7 @@ LORA_HD inline RowGeom row_geom(const PlanDims& d, int rank, int nrows) {
     }
     // more ranges than the reduction can add up (h_in past 256 Ki at rank 256, 2 Mi at
     // rank 8): longer ones, of several passes
-    if ((int64_t)g.krange * kMaxRanges < d.h_in)
+    if ((d.h_in - 1) / kMaxRanges >= g.krange)
         g.krange = round_up_i((d.h_in + kMaxRanges - 1) / kMaxRanges, g.sub);
     g.nsplit = (d.h_in + g.krange - 1) / g.krange;
     g.nlen = expand_nlen(rank, nrows);
@@ -191,7 +191,7 @@ LORA_HD inline bool header_word(const PlanArgs& a, int i, uint32_t& v) {
 // Armed by the workgroup of the row block, a single compute unit wrote all of a large
 // block (29 MB at rank 256, h_in 28672): an update of 32 such rows
 // took 214 us against 7.5, one of 64 rows of rank 128 at 8192 35 against 5.4.
-constexpr int kSliceItems = 64, kMaxSlices = 16;
+constexpr int kSliceItems = 256, kMaxSlices = 16;
 constexpr int kArmQuads = 1024, kArmBlocks = 1024;
 template <bool kStaged>
 __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a);
