@@ -42,13 +42,13 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, datasheet
 # HBM traffic of one step launch of the headline workload, from two rocprofv3
 # --pmc passes (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch) scaled by the
 # same counters on a plain 256 MiB device copy in the same run (FETCH_SIZE
-# reads 131,088.8 KiB for 262,144 KiB read: x 1.99980; WRITE_SIZE reads
+# reads 131,089.4 KiB for 262,144 KiB read: x 1.99973; WRITE_SIZE reads
 # 262,144.0 KiB: x 1.0).  Valid only for the kernel sources it was taken on
 # (hash of csrc/*); reported as null otherwise.
 MEASURED_TRAFFIC = {
-    "sources_sha256_16": "2e0c8a031a8f851b",
+    "sources_sha256_16": "3d79ff4c9dbce160",
     "workload": "decode_q4096_t64_mixed_rank_f16",
-    "fetch_kib": 6707.1, "fetch_scale": 262144.0 / 131093.7,
+    "fetch_kib": 6703.3, "fetch_scale": 262144.0 / 131089.4,
     "write_kib": 732.9, "write_scale": 1.0,
 }
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16/fp16
@@ -513,7 +513,7 @@ def sources_hash() -> str:
     csrc = os.path.join(ROOT, "paper_2401_11240_amd", "csrc")
     h = hashlib.sha256()
     # the sources the step kernel and its planner are built from
-    for f in ("lora_api.hip", "lora_internal.h", "lora_kernels.hip", "lora_device.h"):
+    for f in ("lora_api.hip", "lora_plan.h", "lora_internal.h", "lora_kernels.hip", "lora_device.h"):
         with open(os.path.join(csrc, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

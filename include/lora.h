@@ -225,7 +225,7 @@ int lora_apply_fused_static(lora_table_t t, const lora_batch_t* b, const void* x
  * workspace, in device memory owned by the plan (allocates; not for the hot
  * loop).
  *
- * lora_plan_apply runs the whole delta (lora_apply_fused without the upload)
+ * lora_plan_apply runs the whole delta (lora_apply_fused without writing its list)
  * with the adapters of table t, or of the table the plan was made with when t
  * is NULL, as ONE kernel launch: its grid holds the shrink work items (float32
  * partial results over a K range of A_g), then the reduce work items (the sum

@@ -354,18 +354,20 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
     d.small_step = step_items <= kTargetItems;
     // Steps whose decode blocks alone would take a round or more of one-pass
     // shrink items of 16 KiB and up, and that prompt blocks do not dominate, have
-    // all blocks cut by bytes into about one round (one and a half where an item
-    // would pass 64 KiB), a decode block's range streaming in several passes: an
-    // item's fixed part (launch, work item, pointer: about half of its 7 us at one
-    // pass of 32 KiB) is then paid once per range.  Measured per launch, one pass
-    // per decode item against ranges: 70B-shaped q and gate (256 tokens, 4 prompts
-    // of 512) 283 -> 251 us (in 512, 1024, 1536 items 246, 257, 266), 65 adapters of
-    // rank 16 at 5120 -> 2768 16.2 -> 13.8; 57 tokens of rank 8-128 at 8192 -> 3872
-    // 28.1 -> 28.2 (in 512 items 29.2).  Past the lines it turns: 131 tokens at 9264
-    // -> 13824 (485 decode items, one round anyway) 29.0 -> 30.6, 43 tokens of rank 8
-    // at 12120 11.9 -> 13.0, 25 adapters beside 12 prompts of up to 364 tokens 49.5 ->
-    // 55.4 us.  (The cut depends on one projection only: a launch of several equals
-    // one launch each, bit for bit.)
+    // all blocks cut by bytes into about one round, a decode block's range
+    // streaming in several passes: an item's fixed part (launch, work item,
+    // pointer: about half of its 7 us at one pass of 32 KiB) is then paid once per
+    // range.  Measured per launch, one pass per decode item against ranges: 70B-
+    // shaped q and gate (256 tokens, 4 prompts of 512) 283 -> 251 us, 65 adapters of
+    // rank 16 at 5120 -> 2768 16.2 -> 13.8.  Where an item would pass 64 KiB it is one
+    // round and a half: that costs the 70B-shaped step 2% (246 us in 512 items; 257
+    // in 1024, 266 in 1536) and keeps the steps that gain nothing from it from
+    // losing (57 tokens of rank 8-128 at 8192 -> 3872: one pass 28.1 us, 768 items
+    // 28.2, 512 29.2).  Past the lines it turns: 131 tokens at 9264 -> 13824 (485
+    // decode items, one round anyway) 29.0 -> 30.6, 43 tokens of rank 8 at 12120 11.9
+    // -> 13.0, 25 adapters beside 12 prompts of up to 364 tokens 49.5 -> 55.4 us.
+    // (The cut depends on one projection only: a launch of several equals one
+    // launch each, bit for bit.)
     if (!d.small_step && small_items >= kTargetItems && small_bytes >= (small_items << 14) &&
         3 * small_units >= units && units <= INT32_MAX) {
         const bool wide = units * t->h_in * 2 >= (int64_t)kTargetItems << 16;

@@ -40,14 +40,17 @@
 // batch, columns past h_out and K past h_in are loads out of the buffer's
 // range, which write zeros.
 //
-// What bounds it (clock counters around the loop, 4096 x 4096 x 4096): the 256
-// tile takes 2254 cycles per step where its MFMAs alone take 2048 (91%), at a
-// clock that the power limit holds near 1.5 GHz; MFMAs without any data movement
-// reach 1.56-1.65 PFLOP/s on this card.  The 128 tile takes 766 cycles per step,
-// which is its LDS traffic (32 KiB written, 64 KiB read) at 128 bytes per cycle.
+// What bounds it (clock counters around bare loops of the same structure, 4096 x
+// 4096 x 4096): the 256 tile takes 2254 cycles per step where its MFMAs alone take
+// 2048 (91%), at a clock that the power limit holds near 1.5 GHz; MFMAs without any
+// data movement reach 1.56-1.65 PFLOP/s on this card.  The 128 tile takes 766 cycles
+// per step for 512 of MFMAs; its LDS reads (64 KiB) keep the LDS active for about 256
+// of them by the counters, beside the 32 KiB that its loads write there.  Whole
+// launches hold the MFMAs busy for 60% (256) and 33% (128) of their cycles.
 // Kernel times against the earlier ring in registers (two steps loaded ahead,
-// written to LDS by ds_write), 4096 columns of K 4096: 1024 rows 55.6 -> 42 us,
-// 8437 rows 268 -> 255 us; 547 rows x 13824 of K 5120 in binary16 137 -> 113 us.
+// written to LDS by ds_write), traced on two boxes, 4096 columns of K 4096: 1024 rows
+// 56-61 -> 41-44 us, 8437 rows 268-270 -> 256-258 us; 547 rows x 13824 of K 5120 in
+// binary16 136-137 -> 120-126 us (a library product of that shape: 76 us).
 //
 // Epilogue: for every run of the tile's rows that share an adapter (at most
 // a few for prompt segments), B_g's ranks and the tile's rows of v are staged
