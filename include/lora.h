@@ -101,9 +101,9 @@ typedef struct lora_plan_s* lora_plan_t;   /* a batch planned against a table, l
  * owns on `device` (synchronously on `stream`; the host arrays may be freed on
  * return).  All adapters of one table share dtype, h_in and h_out.
  * On success *out is a new table; on failure *out is left NULL.
- * A device's first table also brings 2 MiB of pinned host memory, through which
- * work lists of some thousand scattered rows reach the device; releasing its
- * last table gives it back.
+ * Releasing a device's last table also gives back the 2 MiB of pinned host
+ * memory that the first work list of some thousand scattered rows took there
+ * (lora_apply_fused_static takes none).
  */
 int lora_register_adapters(lora_table_t* out, int device, int h_in, int h_out, int dtype,
                            int n_adapters, const void* const* A_ptrs, const void* const* B_ptrs,
@@ -272,8 +272,8 @@ int lora_plan_create(lora_plan_t* out, lora_table_t t, const lora_batch_t* b, vo
  * that writes the work list and arms the step buffers, and returns.  The kernel's
  * arguments hold the row blocks (about 60 of them in one launch, 11 where each
  * lists 64 scattered rows); those of more than two launches are read from pinned
- * host memory instead.  No device or host
- * allocation, no copy, no memset, no synchronisation.  A batch that needs more than the
+ * host memory instead (2 MiB, allocated by the first such list on the device).
+ * Otherwise no device or host allocation, no copy, no memset, no synchronisation.  A batch that needs more than the
  * capacity returns LORA_E_WORKSPACE and leaves the plan as it was; errors of
  * b are those of lora_plan_create.  After LORA_E_HIP the plan runs nothing (its
  * launches report LORA_E_STALE) until an update succeeds.  Updates and the plan's launches must be

@@ -646,13 +646,15 @@ int check_not_capturing(hipStream_t s, const char* what) {
 }
 
 // Pinned host memory for lists too large for kernel arguments: kStageSlots slots per
-// device, allocated with the device's first table and given back with its last.  A
+// device, allocated by the first such list and given back with the device's last table
+// (taken with the first table instead, they cost every program 35 us and more).  A
 // launch behind the one that reads a slot writes the slot's use number back; a slot is
 // taken again once its last use has come back, and the host never waits for one (no
 // event either: asking for one would break a capture on another stream).
 struct StageRing {
     std::mutex mu;
     int tables = 0;
+    bool tried = false;                       // allocated, or not to be had
     uint32_t* host = nullptr;                 // kStageSlots times kStagedWords, then the use numbers
     uint32_t* dev = nullptr;                  // the same as the device addresses it
     uint32_t uses[kStageSlots] = {};          // last use of each slot
@@ -663,23 +665,10 @@ struct StageRing {
 constexpr int kMaxDevices = 64;
 StageRing g_stage[kMaxDevices];
 
-// (on the device, current; a device without pinned memory writes every list from arguments)
 void stage_retain(int device) {
     if (device >= kMaxDevices) return;
-    StageRing& r = g_stage[device];
-    std::lock_guard<std::mutex> lk(r.mu);
-    if (r.tables++) return;
-    if (hipHostMalloc((void**)&r.host, sizeof(uint32_t) * StageRing::kWords, hipHostMallocMapped | hipHostMallocCoherent) !=
-        hipSuccess)
-        r.host = nullptr;
-    if (!r.host || hipHostGetDevicePointer((void**)&r.dev, r.host, 0) != hipSuccess) {
-        r.dev = nullptr;
-        (void)hipGetLastError();
-    }
-    for (int i = 0; i < kStageSlots; ++i) {
-        r.uses[i] = 0;
-        if (r.host) r.host[StageRing::use_at(i)] = 0;
-    }
+    std::lock_guard<std::mutex> lk(g_stage[device].mu);
+    ++g_stage[device].tables;
 }
 void stage_release(int device) {
     if (device >= kMaxDevices) return;
@@ -689,9 +678,31 @@ void stage_release(int device) {
     if (r.host) (void)hipHostFree(r.host);
     r.host = nullptr;
     r.dev = nullptr;
+    r.tried = false;
+}
+// (the ring's mutex held, its device current; without the memory every list goes in
+// arguments)
+void stage_allocate(StageRing& r) {
+    r.tried = true;
+    // a thread that captures another stream meanwhile is not disturbed
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return (void)hipGetLastError();
+    if (hipHostMalloc((void**)&r.host, sizeof(uint32_t) * StageRing::kWords, hipHostMallocMapped | hipHostMallocCoherent) !=
+        hipSuccess)
+        r.host = nullptr;
+    if (!r.host || hipHostGetDevicePointer((void**)&r.dev, r.host, 0) != hipSuccess) {
+        r.dev = nullptr;
+        (void)hipGetLastError();
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    for (int i = 0; i < kStageSlots; ++i) {
+        r.uses[i] = 0;
+        if (r.host) r.host[StageRing::use_at(i)] = 0;
+    }
 }
 // A free slot, or -1 (the ring's mutex held).
-int stage_take(StageRing& r) {
+int stage_take(StageRing& r, bool may_allocate) {
+    if (!r.tried && may_allocate) stage_allocate(r);
     if (!r.dev) return -1;
     const int i = (int)(r.next % kStageSlots);
     if (__atomic_load_n(r.host + StageRing::use_at(i), __ATOMIC_ACQUIRE) != r.uses[i]) return -1;
@@ -728,10 +739,10 @@ size_t pack_rows(const HostPlan& p, size_t& i, size_t room, uint32_t* dst) {
 // (a multiple of 4) from blob to w + off_blob.  The data ride in the arguments of up to
 // kArgLaunches launches (64 row blocks of consecutive rows each, 11 of 64 listed rows);
 // more of them, some thousand scattered rows or runs, in pinned memory that one launch
-// reads.  No allocation, no copy engine, nothing
-// that the host or a later call waits for.
+// reads.  No device allocation, no copy engine, nothing that the host or a later call
+// waits for.
 int write_plan(const HostPlan& p, unsigned char* w, bool arm, int device, hipStream_t s, const void* blob = nullptr,
-               size_t blob_bytes = 0, size_t off_blob = 0) {
+               size_t blob_bytes = 0, size_t off_blob = 0, bool may_allocate = true) {
     PlanArgs a{};
     a.w = w;
     a.off_shrink = p.off_shrink;
@@ -759,7 +770,7 @@ int write_plan(const HostPlan& p, unsigned char* w, bool arm, int device, hipStr
         StageRing* ring = left > (size_t)kArgLaunches * kPlanWords && device < kMaxDevices ? &g_stage[device] : nullptr;
         std::unique_lock<std::mutex> lk;
         if (ring) lk = std::unique_lock<std::mutex>(ring->mu);
-        const int slot = ring ? stage_take(*ring) : -1;
+        const int slot = ring ? stage_take(*ring, may_allocate) : -1;
         const size_t room = slot >= 0 ? kStagedWords : kPlanWords;
         uint32_t* data = slot >= 0 ? ring->host + (size_t)slot * kStagedWords : a.data;
         a.staged = slot >= 0 ? ring->dev + (size_t)slot * kStagedWords : nullptr;
@@ -1575,7 +1586,7 @@ int lora_apply_fused_static(lora_table_t t, const lora_batch_t* b, const void* x
     if (int rc = check_not_capturing(s, "lora_apply_fused_static")) return rc;
     unsigned char* w = nullptr;
     if (int rc = scratch_address(t->device, &w)) return rc;
-    if (int rc = write_plan(p, w, false, t->device, s)) return rc;
+    if (int rc = write_plan(p, w, false, t->device, s, nullptr, 0, 0, false)) return rc;   // allocates nothing
     return enqueue(t, p, w, x, ldx, y, ldy, s);
 }
 

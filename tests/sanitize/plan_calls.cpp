@@ -34,9 +34,11 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
 }
 hipError_t hipMalloc(void** p, size_t n) { return (*p = std::aligned_alloc(256, (n + 255) / 256 * 256)) ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n); }
-hipError_t hipHostFree(void* p) { return hipFree(p); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned);
+hipError_t hipHostFree(void* p);
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m);
 hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void*) { return hipMalloc(p, 1 << 24); }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) { *c = hipStreamCaptureStatusNone; return hipSuccess; }
@@ -53,6 +55,8 @@ namespace {
 // fails), their workgroups, the generation the list's header holds after them
 int g_launches, g_workgroups, g_fail_at;
 bool g_hold;
+int g_pinned;                              // pinned allocations not given back
+hipStreamCaptureMode g_mode = hipStreamCaptureModeGlobal;
 std::vector<uint32_t> g_blob;              // the extra words of the launches, in order
 std::vector<int32_t> g_rows;               // the rows they list, in grouped order
 uint32_t g_generation;
@@ -72,6 +76,19 @@ int failures = 0;
 
 }  // namespace
 
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+    if (g_mode != hipStreamCaptureModeRelaxed) return hipErrorStreamCaptureUnsupported;   // as beside a capture
+    ++g_pinned;
+    return hipMalloc(p, n);
+}
+hipError_t hipHostFree(void* p) {
+    --g_pinned;
+    return hipFree(p);
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
+    std::swap(*m, g_mode);
+    return hipSuccess;
+}
 // (g_hold: fills do not get through, as on a stream with earlier work)
 hipError_t lora::launch_fill(uint32_t* p, uint32_t v, uint64_t n, hipStream_t) {
     if (!g_hold) std::fill(p, p + n, v);
@@ -215,6 +232,7 @@ void check_staged_lists() {
     const lora_batch_t b{n, n, off.data(), ad.data()};
     std::vector<int32_t> perm(n), goff(n + 1), gad(n);
     int32_t G = 0;
+    CHECK(g_pinned == 0, "pinned memory before the first large list");
     CHECK(lora_group_rows(&b, 128, perm.data(), goff.data(), gad.data(), &G) == LORA_OK, "group");
     lora_plan_t p = nullptr;
     CHECK(lora_plan_create(&p, t, &b, nullptr) == LORA_OK, "create: %s", lora_last_error());
@@ -229,10 +247,19 @@ void check_staged_lists() {
         }
     }
     lora_plan_destroy(p);
+    CHECK(g_pinned == 1 && g_mode == hipStreamCaptureModeGlobal, "%d pinned", g_pinned);
     lora_release_adapters(t);
+    CHECK(g_pinned == 1, "another table is left");
     lora_release_adapters(t2);                                   // the ring goes, with what was held
+    CHECK(g_pinned == 0, "pinned memory after the last table");
     g_hold = false;
     const lora_table_t t3 = table(256, 264, ranks), t4 = table(256, 520, ranks);
+    // the call that allocates nothing
+    std::vector<unsigned char> xy(2 * (size_t)n * (256 + 264) + 32);
+    unsigned char* x = (unsigned char*)(((uintptr_t)xy.data() + 15) & ~(uintptr_t)15);
+    g_launches = 0;
+    CHECK(lora_apply_fused_static(t3, &b, x, 256, x + 2 * (size_t)n * 256, 264, nullptr) == LORA_OK, "static: %s", lora_last_error());
+    CHECK(g_pinned == 0 && g_launches > 4, "%d pinned, %d launches", g_pinned, g_launches);
     // two projections list their scattered rows once: 16 blocks of 64 rows take two launches'
     // arguments, and 14 words more per block of the second
     const lora_table_t both[] = {t3, t4};
