@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a) {
     const PlanRow r = ((const PlanRow*)data)[block];
     const int32_t* rows = (const int32_t*)data + a.n_rows * kRowWords + (r.row0 >= 0 ? 0 : -1 - r.row0);
     const PlanDims d = *(const PlanDims*)(args + offsetof(PlanArgs, dims) + r.proj() * sizeof(PlanDims));
-    const RowGeom g = row_geom(d, r.rank(), r.nrows());
+    const RowGeom g = row_geom(d, r);
     const DevItem base = row_item(r, g, a.row_first + block, rows);
     const int n_reduce = g.direct ? 0 : g.nslice;
     const int total = g.nsplit + n_reduce + g.ntiles + g.nslice;
@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(kThreads) lora_plan_kernel(PlanArgs a) {
                 v = u32x4{(uint32_t)it.rows[4 * h], (uint32_t)it.rows[4 * h + 1], (uint32_t)it.rows[4 * h + 2],
                           (uint32_t)it.rows[4 * h + 3]};
         ((u32x4*)(a.w + list))[8 * (int64_t)at + part] = v;
-        if (a.step_len && queue >= 0) ((u32x4*)(a.w + a.off_step))[8 * ((int64_t)queue * a.n_xcd + r.home) + part] = v;
+        if (a.step_len && queue >= 0) ((u32x4*)(a.w + a.off_step))[8 * ((int64_t)queue * a.n_xcd + r.home()) + part] = v;
     }
     if (slice) return;
     int32_t* perm = (int32_t*)(a.w + a.off_perm) + r.p0;
@@ -388,7 +388,8 @@ int plan_lists(const lora_table_s* t, const lora_batch_t* b, HostPlan& p) {
             PlanRow row{};
             row.group = g;
             row.adapter = p.group_adapter[g];
-            row.shape = r | nb << 16;
+            row.shape = (int32_t)((uint32_t)(r | nb << 16) | (uint32_t)(q.sub / 32) << 26);
+            row.cut = q.krange / q.sub << 8;
             row.p0 = p0;
             // the last row is nb - 1 past the first only when all are consecutive (rows ascend)
             row.row0 = p.perm[p0 + nb - 1] == p.perm[p0] + nb - 1 ? p.perm[p0] : -1;
@@ -489,9 +490,9 @@ int plan_layout(const lora_table_s* t, HostPlan& p) {
             for (int kind = 0; kind < 3; ++kind)
                 for (int i = 0; i < p.n_rb; ++i) {
                     PlanRow& r = p.rows[i];
-                    const RowGeom q = row_geom(p.dims[r.proj()], r.rank(), r.nrows());
+                    const RowGeom q = row_geom(p.dims[r.proj()], r);
                     int& u = at[home[i]];
-                    r.home = home[i];
+                    r.cut |= kind == 0 ? home[i] : 0;
                     (kind == 0 ? r.step_shrink : (kind == 1 ? r.step_reduce : r.step_expand)) = u;
                     u += kind == 0 ? q.nsplit : (kind == 1 ? (q.direct ? 0 : q.nslice) : q.ntiles);
                 }
@@ -552,10 +553,10 @@ void list_items(const HostPlan& p, std::vector<DevItem>& grid, std::vector<DevIt
     for (int i = 0; i < p.n_rb; ++i) {
         const PlanRow& r = p.rows[i];
         const PlanDims& d = p.dims[r.proj()];
-        const RowGeom g = row_geom(d, r.rank(), r.nrows());
+        const RowGeom g = row_geom(d, r);
         const DevItem base = row_item(r, g, i, p.perm.data() + r.p0);
         auto slot = [&](int queue, int list) -> DevItem& {
-            return grid[p.step_len ? (size_t)queue * p.n_xcd + r.home : (size_t)list];
+            return grid[p.step_len ? (size_t)queue * p.n_xcd + r.home() : (size_t)list];
         };
         for (int c = 0; c < g.nsplit; ++c) {
             DevItem it = base;

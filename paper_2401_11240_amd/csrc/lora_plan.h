@@ -27,17 +27,20 @@ struct PlanDims {
 // One row block, as the host passes it.
 struct PlanRow {
     int32_t group, adapter;
-    int32_t shape;           // rank | rows << 16 | projection << 24
+    int32_t shape;           // rank | rows << 16 | projection << 24 | K per pass / 32 << 26
     int32_t p0;              // position of the first row in the grouped row order
     int32_t row0;            // the first row when they are consecutive; else -1 - (their place in the row
                              // list, where a projection past the first passes only inline rows)
     uint32_t part;           // float offset of its first partial block
     int32_t shrink_at, reduce_at, expand_at, all_at;   // its first item in each list
-    int32_t home;            // XCD, and its first items in that XCD's queue (grid laid out per XCD)
-    int32_t step_shrink, step_reduce, step_expand;
+    int32_t cut;             // XCD (grid laid out per XCD) | passes per K range << 8
+    int32_t step_shrink, step_reduce, step_expand;   // its first items in that XCD's queue
     LORA_HD int rank() const { return shape & 0xffff; }
     LORA_HD int nrows() const { return (shape >> 16) & 0xff; }
-    LORA_HD int proj() const { return shape >> 24; }
+    LORA_HD int proj() const { return (shape >> 24) & 3; }
+    LORA_HD int sub() const { return (int)((uint32_t)shape >> 26) * 32; }
+    LORA_HD int home() const { return cut & 0xff; }
+    LORA_HD int krange() const { return (cut >> 8) * sub(); }
     // rows in the row list: not the consecutive ones, and once for all projections where
     // only the grouped row order holds them
     LORA_HD int listed() const { return row0 < 0 && (proj() == 0 || nrows() <= kInlineRows) ? nrows() : 0; }
@@ -54,25 +57,30 @@ struct RowGeom {
     int slen, nslice;             // reduce: floats per item, items
 };
 
-LORA_HD inline RowGeom row_geom(const PlanDims& d, int rank, int nrows) {
-    RowGeom g;
-    g.sub = shrink_sub(rank, nrows);
-    g.krange = g.sub;
+// Its K ranges, `sub` K per pass (chosen on the host; a row block carries them).
+inline void row_cut(const PlanDims& d, int rank, int nrows, int& sub, int& krange) {
+    sub = shrink_sub(rank, nrows);
+    krange = sub;
     if (nrows > kInlineRows) {
         const int per = (d.h_in + d.big_split - 1) / d.big_split;
-        g.krange = round_up_i(max_i(per, g.sub), g.sub);
+        krange = round_up_i(max_i(per, sub), sub);
     }
     // (never more ranges than without the cut by bytes, so that a step it is taken
     // for needs no more memory: a plan or workspace that holds a batch holds its parts)
     if (d.items > 0 && (nrows > kInlineRows || shrink_can_dma(rank, nrows))) {
         const int n = (int)((int64_t)(nrows + rank) * d.items / d.units);
         const int per = n > 1 ? (d.h_in + n - 1) / n : d.h_in;
-        g.krange = max_i(g.krange, round_up_i(per, g.sub));
+        krange = max_i(krange, round_up_i(per, sub));
     }
     // more ranges than the reduction can add up (h_in past 256 Ki at rank 256, 2 Mi at
     // rank 8): longer ones, of several passes
-    if ((d.h_in - 1) / kMaxRanges >= g.krange)
-        g.krange = round_up_i((d.h_in + kMaxRanges - 1) / kMaxRanges, g.sub);
+    if ((d.h_in - 1) / kMaxRanges >= krange) krange = round_up_i((d.h_in + kMaxRanges - 1) / kMaxRanges, sub);
+}
+
+LORA_HD inline RowGeom row_geom(const PlanDims& d, int rank, int nrows, int sub, int krange) {
+    RowGeom g;
+    g.sub = sub;
+    g.krange = krange;
     g.nsplit = (d.h_in + g.krange - 1) / g.krange;
     g.nlen = expand_nlen(rank, nrows);
     g.ntiles = (d.h_out + g.nlen - 1) / g.nlen;
@@ -90,6 +98,14 @@ LORA_HD inline RowGeom row_geom(const PlanDims& d, int rank, int nrows) {
     g.slen = min_i(round_up_i((g.pstride + nslice - 1) / nslice, 4), 4 * (kThreads / gmin));
     g.nslice = (g.pstride + g.slen - 1) / g.slen;
     return g;
+}
+inline RowGeom row_geom(const PlanDims& d, int rank, int nrows) {
+    int sub, krange;
+    row_cut(d, rank, nrows, sub, krange);
+    return row_geom(d, rank, nrows, sub, krange);
+}
+LORA_HD inline RowGeom row_geom(const PlanDims& d, const PlanRow& r) {
+    return row_geom(d, r.rank(), r.nrows(), r.sub(), r.krange());
 }
 
 // What every item of the row block (number rb) carries; rows: its rows when they
