@@ -206,7 +206,7 @@ LORA_HD inline bool header_word(const PlanArgs& a, int i, uint32_t& v) {
 // hundred KB of items out: about 3 us, the launch, where the step buffers are small.
 // Armed by the workgroup of the row block, a single compute unit wrote all of a large
 // block (29 MB at rank 256, h_in 28672): an update of 32 such rows
-// took 214 us against 7.5, one of 64 rows of rank 128 at 8192 35 against 5.4.
+// took 214 us against 8.5, one of 64 rows of rank 128 at 8192 35 against 6.4.
 constexpr int kSliceItems = 256, kMaxSlices = 16;
 constexpr int kArmQuads = 1024, kArmBlocks = 1024;
 template <bool kStaged>
